@@ -84,31 +84,21 @@ __global__ void __launch_bounds__(256) k_profile_adj_units(ProfParams q, const f
   __shared__ float2 qd[128 * 4];
   __shared__ int bq[64 * 4];
   __shared__ int qk[LS == FDTBX_LINESHAPE_HOSEMANN ? 128 * 4 : 1];  // node indices (support edge)
-  const int wv = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
+  const int wv = (int)(threadIdx.x >> 6);
   const int64_t U = T.meta[1];
   const int64_t total = U > 0 ? min(T.meta[0], T.max_units) : 0;
-  const int home = (int)(blockIdx.x % kXcds);
-  for (int k = 0; k < kXcds; ++k) {
-    const int x = (home + k) % kXcds;
-    int64_t qb, qe;
-    queue_span(T, x, total, &qb, &qe);
-    for (;;) {
-      int got = 0;
-      if (lane == 0) got = atomicAdd(&T.ctr[x], 1);
-      const int64_t u = qb + (int64_t)__builtin_amdgcn_readfirstlane(got);
-      if (u >= qe) break;  // uniform
-      int64_t p0, p1;
-      const int t = unit_range(q, T, offsets, u, U, &p0, &p1);
-      if (t < 0) continue;
-      adjoint_range<LS>(q, refl, nodes, pix, tile, idx, grad_image, n_hkl, sums, partials, t, p0, p1, 64,
-                        qn + 128 * wv, qd + 128 * wv, bq + 64 * wv,
-                        LS == FDTBX_LINESHAPE_HOSEMANN ? qk + 128 * wv : nullptr);
-    }
-  }
+  for_units(T, total, [&](int64_t u) {
+    int64_t p0, p1;
+    const int t = unit_range(q, T, offsets, u, U, &p0, &p1);
+    if (t < 0) return;
+    adjoint_range<LS>(q, refl, nodes, pix, tile, idx, grad_image, n_hkl, sums, partials, t, p0, p1, 64, qn + 128 * wv,
+                      qd + 128 * wv, bq + 64 * wv, LS == FDTBX_LINESHAPE_HOSEMANN ? qk + 128 * wv : nullptr);
+  });
 }
 
-__global__ void k_zero_i32(int32_t* __restrict__ v, int n) {
-  if ((int)threadIdx.x < n) v[threadIdx.x] = 0;
+// Clears the queue counters, one per lane of one wave.
+__global__ void k_zero_queues(int32_t* __restrict__ ctr) {
+  if (threadIdx.x < kQueues) ctr[threadIdx.x * kQueueStride] = 0;
 }
 
 template <int LS>
@@ -128,7 +118,7 @@ static int launch_adj_units(const ProfParams& q, const float* refl, const float*
 }
 
 // The balanced adjoint over the units that the balanced forward launch with the same model,
-// lists, order and pair_cap left in units_ws; ctr: 8 int32 of device memory for its queues.
+// lists, order and pair_cap left in units_ws; ctr: kQueueBytes of device memory for its queues.
 // The sums (or partials) must be cleared by the caller.
 int launch_adjoint_units(const fdtbx_model* model, const float* refl, const float* nodes, const double* pix,
                          const double* tile, const int64_t* offsets, const int32_t* idx, const int32_t* order,
@@ -139,7 +129,7 @@ int launch_adjoint_units(const fdtbx_model* model, const float* refl, const floa
   const UnitLayout L = unit_layout(q, order != nullptr, pair_cap, model->geom.unit_pairs);
   UnitTable T = unit_view(L, order, model->geom.unit_pairs, const_cast<void*>(units_ws));
   T.ctr = ctr;
-  hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s, ctr, kXcds);
+  hipLaunchKernelGGL(k_zero_queues, dim3(1), dim3(64), 0, s, ctr);
   FDTBX_LAUNCH_CHECK("balanced adjoint counters");
   if (q.lineshape == FDTBX_LINESHAPE_GAUSSIAN)
     return launch_adj_units<FDTBX_LINESHAPE_GAUSSIAN>(q, refl, nodes, pix, tile, offsets, idx, grad_image, n_hkl, sums,

@@ -7,6 +7,7 @@
 #include <mutex>
 
 #include "internal.h"
+#include "profile_common.h"
 
 namespace fdtbx {
 
@@ -305,15 +306,21 @@ extern "C" int fdtbx_profile_pattern_async(const fdtbx_model* model, const int32
   return stamp(7);
 }
 
+// Bytes of the backward workspace after the per-reflection sums: the finishing pass's partials,
+// dF2 when the caller wants none, and the structure factor adjoint's, all of them written after
+// the adjoint launch.  That launch's queue counters lie at the start of the same bytes, so that
+// they add nothing but where the problem is tiny.
+static size_t backward_tail(int64_t n_hkl, int64_t n_atoms) {
+  size_t b = align_up(fdtbx_adjoint_finish_workspace(n_hkl), 256);
+  b += align_up((size_t)n_hkl * sizeof(float), 256);
+  if (n_atoms > 0) b += align_up(fdtbx_sf_adjoint_workspace(n_hkl, n_atoms), 256);
+  return b > kQueueBytes ? b : kQueueBytes;
+}
+
 extern "C" size_t fdtbx_backward_workspace(int64_t n_hkl, int64_t n_atoms) {
   if (n_hkl < 0) return 0;
   if (n_hkl == 0) return 256;  // nothing is used; a non-zero size keeps callers' allocations valid
-  size_t b = align_up((size_t)n_hkl * 6 * sizeof(double), 256);
-  b += align_up(fdtbx_adjoint_finish_workspace(n_hkl), 256);
-  b += align_up((size_t)n_hkl * sizeof(float), 256);
-  b += 256;  // queue counters of the balanced adjoint launch
-  if (n_atoms > 0) b += align_up(fdtbx_sf_adjoint_workspace(n_hkl, n_atoms), 256);
-  return b;
+  return align_up((size_t)n_hkl * 6 * sizeof(double), 256) + backward_tail(n_hkl, n_atoms);
 }
 
 extern "C" int fdtbx_pattern_backward(const fdtbx_model* model, const int32_t* hkl, int64_t n_hkl, const float* F,
@@ -360,8 +367,7 @@ extern "C" int fdtbx_pattern_backward(const fdtbx_model* model, const int32_t* h
   w += align_up(fin_bytes, 256);
   float* g2 = dF2 ? dF2 : (float*)w;
   w += align_up((size_t)n_hkl * sizeof(float), 256);
-  int32_t* ctr = (int32_t*)w;
-  w += 256;
+  int32_t* ctr = (int32_t*)fin;  // used up before the finishing pass writes there
   hipStream_t s = (hipStream_t)stream;
   rc = fill(sums, 6 * n_hkl, 0.0, s);
   if (rc) return rc;
@@ -431,10 +437,9 @@ extern "C" int fdtbx_pattern_backward_deterministic(
   w += align_up(fin_bytes, 256);
   float* g2 = dF2 ? dF2 : (float*)w;
   w += align_up((size_t)n_hkl * sizeof(float), 256);
-  int32_t* ctr = (int32_t*)w;
-  w += 256;
+  int32_t* ctr = (int32_t*)fin;  // used up before the finishing pass writes there
   void* sfw = w;
-  if (atoms) w += align_up(fdtbx_sf_adjoint_workspace(n_hkl, n_atoms), 256);
+  w = (char*)fin + backward_tail(n_hkl, atoms ? n_atoms : 0);
   float* partials = (float*)w;
   w += align_up((size_t)pair_cap * 12 * sizeof(float), 256);
   int64_t* refl_ptr = (int64_t*)w;

@@ -207,7 +207,7 @@ int launch_balanced(const fdtbx_model* model, const float* refl, const float* no
                     int64_t pair_cap, float* image, void* ws, size_t ws_bytes, hipStream_t s);
 
 // Balanced adjoint (adjoint.hip) over the unit tables a balanced forward launch left in
-// units_ws; ctr: 8 int32 of device scratch; sums or partials cleared by the caller.
+// units_ws; ctr: kQueueBytes of device scratch; sums or partials cleared by the caller.
 int launch_adjoint_units(const fdtbx_model* model, const float* refl, const float* nodes, const double* pix,
                          const double* tile, const int64_t* offsets, const int32_t* idx, const int32_t* order,
                          int64_t pair_cap, const void* units_ws, int32_t* ctr, int64_t n_hkl, const float* grad_image,

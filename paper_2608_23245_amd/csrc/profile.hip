@@ -129,7 +129,7 @@ __global__ void __launch_bounds__(256) k_unit_count(ProfParams q, UnitTable T, c
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t U = T.fixed_U > 0 ? T.fixed_U : default_unit_pairs(offsets[n_tiles]);
   if (p == 0) T.meta[1] = U;
-  if (p < kXcds) T.ctr[p] = 0;
+  if (p < kQueues) T.ctr[p * kQueueStride] = 0;
   if (p >= kXcds * T.nj) return;
   const int64_t b = (p % T.nj) * kXcds + p / T.nj;
   const int t = slot_tile(q, T, b);
@@ -148,8 +148,7 @@ __global__ void __launch_bounds__(256) k_unit_fill(ProfParams q, UnitTable T, co
   for (int64_t k = 0; k < n && s + k < T.max_units; ++k) T.unit_slot[s + k] = (int32_t)b;
 }
 
-// Persistent: every wave takes units from its XCD's queue, then from the following queues,
-// until all are empty (the exit every wave reaches: each queue's counter only grows).
+// Persistent: every wave takes units until none is left (for_units).
 template <int LS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) k_profile_units(ProfParams q, const float* __restrict__ refl,
                                                        const float* __restrict__ nodes, const double* __restrict__ pix,
@@ -162,26 +161,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) k
   const int wv = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
   const int64_t U = T.meta[1];
   const int64_t total = U > 0 ? min(T.meta[0], T.max_units) : 0;
-  const int home = (int)(blockIdx.x % kXcds);
-  for (int k = 0; k < kXcds; ++k) {
-    const int x = (home + k) % kXcds;
-    int64_t qb, qe;
-    queue_span(T, x, total, &qb, &qe);
-    for (;;) {
-      int got = 0;
-      if (lane == 0) got = atomicAdd(&T.ctr[x], 1);
-      const int64_t u = qb + (int64_t)__builtin_amdgcn_readfirstlane(got);
-      if (u >= qe) break;  // uniform
-      int64_t p0, p1;
-      const int t = unit_range(q, T, offsets, u, U, &p0, &p1);
-      if (t < 0) continue;
-      const TilePixel px = tile_pixel(q, pix, tile, t, lane);
-      unsigned long long cnt = 0;
-      partials[u * 64 + lane] = pairs_sum<false, LS>(q, refl, nodes, idx, px.box, px.R, px.Z, p0, p1, 64,
-                                                     qn + 256 * wv, bq + 64 * wv, cnt,
-                                                     LS == FDTBX_LINESHAPE_HOSEMANN ? qk + 128 * wv : nullptr);
-    }
-  }
+  for_units(T, total, [&](int64_t u) {
+    int64_t p0, p1;
+    const int t = unit_range(q, T, offsets, u, U, &p0, &p1);
+    if (t < 0) return;
+    const TilePixel px = tile_pixel(q, pix, tile, t, lane);
+    unsigned long long cnt = 0;
+    partials[u * 64 + lane] = pairs_sum<false, LS>(q, refl, nodes, idx, px.box, px.R, px.Z, p0, p1, 64, qn + 256 * wv,
+                                                   bq + 64 * wv, cnt,
+                                                   LS == FDTBX_LINESHAPE_HOSEMANN ? qk + 128 * wv : nullptr);
+  });
 }
 
 // Per launched tile: its units' pixel sums added in unit order, times the Lorentz factor,
