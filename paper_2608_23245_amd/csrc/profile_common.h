@@ -71,13 +71,27 @@ __device__ inline int tile_of_block(const ProfParams& q, int b) {
 __host__ __device__ inline int64_t ceil_div_dev(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Pairs per work unit of the balanced launch (fdtbx_profile_balanced) for a launch of n_pairs
-// culled pairs: at most 2^19 units in all besides one partial unit per tile (64 per wave of
-// 256 compute units with 32 waves each), at least 32 pairs.  A function of the pair count
-// alone, so that the image does not depend on the device.
-constexpr int64_t kUnitTarget = int64_t{1} << 19;
+// culled pairs, a function of the pair count alone, so that the image does not depend on the
+// device.  A unit's cost besides its pairs (its queue entry, pixel coordinates, a set-up that
+// fills only U of the 64 lanes, 256 bytes of sums) is about a third of a pair's, so 16 pairs lose
+// little, and a launch needs more units than the 7168 waves of a card to fill it: as many units
+// as 8192 where that takes fewer than 16 pairs each, and at most 2^19 units besides one partial
+// unit per tile.  Forward / adjoint at 1, 4, 16, 32, 64 pairs: 2,380 pairs 66/63/127/222/283 and
+// 56/76/199/366/473 us; 33,424 pairs 162/113/131/179/289 and 145/138/201/287/457 us; 490,639
+// pairs 1206/519/413/445/551 and 967/580/551/630/772 us; 28.9 million pairs 72.5/54.0/50.5/50.0/
+// 50.8 and 134/121/120/120/122 ms.
+constexpr int64_t kUnitTarget = int64_t{1} << 19, kUnitFew = 8192, kUnitPairs = 16;
 __host__ __device__ inline int64_t default_unit_pairs(int64_t n_pairs) {
-  const int64_t U = (n_pairs + kUnitTarget - 1) / kUnitTarget;
-  return U < 32 ? 32 : U;
+  if (n_pairs == 0) return 32;  // no unit at all: any size will do
+  const int64_t few = (n_pairs + kUnitFew - 1) / kUnitFew, most = (n_pairs + kUnitTarget - 1) / kUnitTarget;
+  const int64_t U = few < kUnitPairs ? few : kUnitPairs;
+  return U < most ? most : U;
+}
+// The most units (besides one per tile) that default_unit_pairs gives for at most cap pairs.
+inline int64_t most_units(int64_t cap) {
+  const int64_t few = cap < kUnitFew ? cap : kUnitFew, n = ceil_div(cap, kUnitPairs);
+  const int64_t many = n < kUnitTarget ? n : kUnitTarget;
+  return few > many ? few : many;
 }
 
 // Mirror folds.  Tile column tiles_x - 1 - tx holds the left-right mirror pixels of column tx
@@ -466,10 +480,8 @@ inline UnitLayout unit_layout(const ProfParams& q, bool has_order, int64_t pair_
   UnitLayout L;
   L.n_slots = has_order ? order_grid(q.lcols, q.lrows) : tile_grid(q);
   L.nj = ceil_div(L.n_slots, kXcds);
-  // sum over tiles of ceil(len / U) <= pair_cap / U + n_slots, and U >= 32 with U >= n_pairs / 2^19
-  // when it is the library's choice
-  const int64_t by_cap = ceil_div(pair_cap, fixed_U > 0 ? fixed_U : 32);
-  L.max_units = (fixed_U > 0 ? by_cap : (by_cap < kUnitTarget ? by_cap : kUnitTarget)) + L.n_slots;
+  // sum over tiles of ceil(len / U) <= pair_cap / U + n_slots
+  L.max_units = (fixed_U > 0 ? ceil_div(pair_cap, fixed_U) : most_units(pair_cap)) + L.n_slots;
   size_t o = 0;
   L.qscan = o;
   o += align_up((size_t)(kXcds * L.nj) * sizeof(int64_t), 256);

@@ -38,14 +38,12 @@ def crop():
 
 
 def cut(off, idx, total):
-    """The first pairs of every tile's list, dealt over the tiles, total in all."""
-    n = off.shape[0] - 1
-    want = np.full(n, total // n) + (np.arange(n) < total % n)
-    assert np.all(want <= np.diff(off))
-    parts = [idx[off[t]:off[t] + want[t]] for t in range(n)]
-    o = np.concatenate([[0], np.cumsum(want)])
-    i = np.concatenate(parts) if total else np.zeros(1, dtype=np.int32)
-    return torch.as_tensor(o, dtype=torch.int64).cuda(), torch.as_tensor(i, dtype=torch.int32).cuda()
+    """total of the lists' pairs, spread evenly over them, as lists of the same tiles."""
+    pick = np.linspace(0, idx.shape[0] - 1, total).astype(np.int64)
+    assert np.unique(pick).shape[0] == total
+    tile_of = np.searchsorted(off, pick, side="right") - 1
+    o = np.concatenate([[0], np.cumsum(np.bincount(tile_of, minlength=off.shape[0] - 1))])
+    return torch.as_tensor(o, dtype=torch.int64).cuda(), torch.as_tensor(idx[pick], dtype=torch.int32).cuda()
 
 
 @pytest.mark.parametrize("total", [1, 64, 65] + [1024 * w + d for w in range(4, 9) for d in (-1, 0, 1)])
