@@ -30,17 +30,32 @@ __device__ static inline cplx cdiv(cplx a, cplx b) {
   return {(a.re * b.re + a.im * b.im) / d, (a.im * b.re - a.re * b.im) / d};
 }
 
-// a_{n}, n = 1..kWN, into coef[0..kWN-1]; called by threads 0..kWN-1 of a block.
-__device__ static double weideman_coef(int n, double L) {
+// a_1 .. a_kWN.  They depend on nothing, so the host forms them once and every launch carries
+// them in its arguments: the Horner loops then read them as scalars.  (Formed by every block on
+// the device, 159 tangents, exponentials and cosines one after another, they were 65 of the
+// 75 us of a 16 x 16 node table.)
+struct WeidemanCoef {
+  double a[kWN];
+};
+
+static WeidemanCoef form_weideman_coef() {
   const int M = 2 * kWN, M2 = 2 * M;
-  double sum = 0.0;
-  for (int k = -M + 1; k <= M - 1; ++k) {
-    double th = k * M_PI / M;
-    double t = L * tan(0.5 * th);
-    double f = exp(-t * t) * (L * L + t * t);
-    sum += f * cos(n * th);
+  const double L = sqrt(kWN / sqrt(2.0));
+  WeidemanCoef c;
+  for (int n = 1; n <= kWN; ++n) {
+    double sum = 0.0;
+    for (int k = -M + 1; k <= M - 1; ++k) {
+      const double th = k * M_PI / M, t = L * tan(0.5 * th);
+      sum += exp(-t * t) * (L * L + t * t) * cos(n * th);
+    }
+    c.a[n - 1] = sum / M2;  // the theta = -pi sample has f = 0
   }
-  return sum / M2;  // the theta = -pi sample has f = 0
+  return c;
+}
+
+static const WeidemanCoef& weideman_coef() {
+  static const WeidemanCoef c = form_weideman_coef();
+  return c;
 }
 
 // w(z) and w'(z) (Im z >= 0).
@@ -212,22 +227,20 @@ __device__ static void node_record(const NodeParams& p, int k, const double* coe
   o[7] = (float)d2;
 }
 
-__global__ void __launch_bounds__(256) k_nodes(NodeParams p, float* __restrict__ out) {
-  __shared__ double coef[kWN];
+// One wave per block: a table of n <= 96 nodes per side then spreads over more compute units
+// than its 256-thread blocks would (the work of a node is a serial chain of binary64 FMAs).
+__global__ void __launch_bounds__(64) k_nodes(NodeParams p, WeidemanCoef wc, float* __restrict__ out) {
   const double L = sqrt(kWN / sqrt(2.0));
-  if (threadIdx.x < kWN && p.sig != 0.0) coef[threadIdx.x] = weideman_coef(threadIdx.x + 1, L);
-  __syncthreads();
   int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k < p.n * p.n)
-    node_record(p, k, coef, L, out + (int64_t)FDTBX_NODE_FLOATS * k);
+    node_record(p, k, wc.a, L, out + (int64_t)FDTBX_NODE_FLOATS * k);
   else if (k < node_rows(p.n))
     block_record(p, k - p.n * p.n, out + (int64_t)FDTBX_NODE_FLOATS * k);
 }
 
 // Batched models: block b of node_blocks covers nodes [first, first + 256) of one model.
 __global__ void __launch_bounds__(256) k_b_nodes(const fdtbx_batch_entry* __restrict__ ent, const int64_t* __restrict__ blocks,
-                                                 float* __restrict__ out) {
-  __shared__ double coef[kWN];
+                                                 WeidemanCoef wc, float* __restrict__ out) {
   const int64_t item = blocks[blockIdx.x];
   const int m = (int)(item >> 40);
   const int k = (int)(item & ((1ll << 40) - 1)) + threadIdx.x;
@@ -240,18 +253,16 @@ __global__ void __launch_bounds__(256) k_b_nodes(const fdtbx_batch_entry* __rest
   p.sig = e.model.dis.sigma_theta;
   p.gam = e.model.dis.gamma_theta;
   const double L = sqrt(kWN / sqrt(2.0));
-  if (threadIdx.x < kWN && p.sig != 0.0) coef[threadIdx.x] = weideman_coef(threadIdx.x + 1, L);
-  __syncthreads();
   float* o = out + (int64_t)FDTBX_NODE_FLOATS * (e.node_off + k);
   if (k < p.n * p.n)
-    node_record(p, k, coef, L, o);
+    node_record(p, k, wc.a, L, o);
   else if (k < node_rows(p.n))
     block_record(p, k - p.n * p.n, o);
 }
 
 int launch_batch_nodes(const fdtbx_batch_entry* ent, const int64_t* blocks, int64_t n_nb, float* nodes, hipStream_t s) {
   if (n_nb <= 0) return FDTBX_OK;
-  hipLaunchKernelGGL(k_b_nodes, dim3((unsigned)n_nb), dim3(256), 0, s, ent, blocks, nodes);
+  hipLaunchKernelGGL(k_b_nodes, dim3((unsigned)n_nb), dim3(256), 0, s, ent, blocks, weideman_coef(), nodes);
   FDTBX_LAUNCH_CHECK("batch nodes");
   return FDTBX_OK;
 }
@@ -282,7 +293,8 @@ extern "C" int fdtbx_node_table(const fdtbx_disorder* dis, const fdtbx_quadratur
   p.sig = dis->sigma_theta;
   p.gam = dis->gamma_theta;
   const int64_t rows = node_rows(p.n);
-  hipLaunchKernelGGL(k_nodes, dim3((unsigned)ceil_div(rows, 256)), dim3(256), 0, (hipStream_t)stream, p, nodes);
+  hipLaunchKernelGGL(k_nodes, dim3((unsigned)ceil_div(rows, 64)), dim3(64), 0, (hipStream_t)stream, p, weideman_coef(),
+                     nodes);
   FDTBX_LAUNCH_CHECK("node table");
   return FDTBX_OK;
 }
