@@ -545,7 +545,8 @@ __global__ void k_sb_boxes(CullParams q, const double* __restrict__ tile, double
   sb[8 * (int64_t)s + 7] = 0.0;
 }
 
-// One wave per 64 reflections; loops over all superblocks and writes one mask word each.
+// One wave per 64 reflections and share of the superblocks (gridDim.y shares): it loops over
+// them and writes one mask word each.
 __global__ void __launch_bounds__(64) k_sb_mask(CullParams q, const double* __restrict__ sb, const double* __restrict__ cull,
                                                 uint64_t* __restrict__ mask) {
   int64_t w = blockIdx.x;
@@ -553,8 +554,9 @@ __global__ void __launch_bounds__(64) k_sb_mask(CullParams q, const double* __re
   double c[13];
   bool have = r < q.n_hkl;
   for (int k = 0; k < 13; ++k) c[k] = have ? cull[FDTBX_CULL_DOUBLES * r + k] : 0.0;
-  const int nsb = q.sb_x * q.sb_y;
-  for (int s = 0; s < nsb; ++s) {
+  const int nsb = q.sb_x * q.sb_y, per = (nsb + (int)gridDim.y - 1) / (int)gridDim.y;
+  const int s1 = min(nsb, per * ((int)blockIdx.y + 1));
+  for (int s = per * (int)blockIdx.y; s < s1; ++s) {
     if ((s % q.sb_x) * kSB >= q.lcols || (s / q.sb_x) * kSB >= q.lrows) continue;  // no tile of it gets a list
     double box[6];
     for (int k = 0; k < 6; ++k) box[k] = sb[8 * (int64_t)s + k];
@@ -779,6 +781,14 @@ static void cull_params(const fdtbx_geometry* g, int64_t n_hkl, CullParams* q) {
   q->n_words = ceil_div(n_hkl, 64);
 }
 
+// Shares of the superblocks in the mask launch: as many as make 4096 waves (a short reflection
+// list alone gives too few to hide the latency of their loads: 8 waves took 305 us for 514
+// reflections and 650 superblocks), one where the list alone does.
+static unsigned mask_shares(const CullParams& q) {
+  const int64_t nsb = (int64_t)q.sb_x * q.sb_y, want = ceil_div(4096, q.n_words);
+  return (unsigned)(want < nsb ? want : nsb);
+}
+
 // Workspace: superblock boxes | masks | tile counts scratch.
 static size_t cull_workspace_of(const CullParams& q) {
   int64_t nsb = (int64_t)q.sb_x * q.sb_y;
@@ -813,7 +823,7 @@ static int cull_lists(const CullParams& q, const double* tile, const double* cul
   int32_t* part = (int32_t*)w;
   hipLaunchKernelGGL(k_sb_boxes, dim3((unsigned)ceil_div(nsb, 256)), dim3(256), 0, s, q, tile, sb);
   FDTBX_LAUNCH_CHECK("cull superblocks");
-  hipLaunchKernelGGL(k_sb_mask, dim3((unsigned)q.n_words), dim3(64), 0, s, q, sb, cull, mask);
+  hipLaunchKernelGGL(k_sb_mask, dim3((unsigned)q.n_words, mask_shares(q)), dim3(64), 0, s, q, sb, cull, mask);
   FDTBX_LAUNCH_CHECK("cull masks");
   hipLaunchKernelGGL(k_tile_lists<0>, dim3((unsigned)nsb), dim3(64 * kTB), 0, s, q, tile, mask, cull, offsets, part,
                      (int32_t*)nullptr, (const int64_t*)nullptr, (int64_t)0);
@@ -965,7 +975,7 @@ int cull_on_device(const fdtbx_geometry* geom, const double* tile, int64_t n_hkl
   int32_t* part = (int32_t*)w;
   hipLaunchKernelGGL(k_sb_boxes, dim3((unsigned)ceil_div(nsb, 256)), dim3(256), 0, s, q, tile, sb);
   FDTBX_LAUNCH_CHECK("cull superblocks");
-  hipLaunchKernelGGL(k_sb_mask, dim3((unsigned)q.n_words), dim3(64), 0, s, q, sb, cull, mask);
+  hipLaunchKernelGGL(k_sb_mask, dim3((unsigned)q.n_words, mask_shares(q)), dim3(64), 0, s, q, sb, cull, mask);
   FDTBX_LAUNCH_CHECK("cull masks");
   hipLaunchKernelGGL(k_tile_lists<0>, dim3((unsigned)nsb), dim3(64 * kTB), 0, s, q, tile, mask, cull, offsets, part,
                      (int32_t*)nullptr, (const int64_t*)nullptr, (int64_t)0);
