@@ -43,11 +43,12 @@ __global__ void __launch_bounds__(64 * WAVES) k_profile_adj(ProfParams q, const 
                                                             const int32_t* __restrict__ order) {
   __shared__ float4 qn[128 * WAVES];
   __shared__ float2 qd[128 * WAVES];
+  __shared__ __align__(16) float gw[128 * WAVES];
   __shared__ int bq[64 * WAVES];
   __shared__ int qk[LS == FDTBX_LINESHAPE_HOSEMANN ? 128 * WAVES : 1];  // node indices (support edge)
   const int t = order ? order[blockIdx.x] : tile_of_block(q, blockIdx.x);
   if (t < 0) return;
-  adjoint_tile<LS, WAVES>(q, refl, nodes, pix, tile, offsets, idx, grad_image, n_hkl, sums, partials, t, qn, qd, bq,
+  adjoint_tile<LS, WAVES>(q, refl, nodes, pix, tile, offsets, idx, grad_image, n_hkl, sums, partials, t, qn, qd, bq, gw,
                           LS == FDTBX_LINESHAPE_HOSEMANN ? qk : nullptr);
 }
 
@@ -82,6 +83,7 @@ __global__ void __launch_bounds__(256) k_profile_adj_units(ProfParams q, const f
                                                            UnitTable T) {
   __shared__ float4 qn[128 * 4];
   __shared__ float2 qd[128 * 4];
+  __shared__ __align__(16) float gw[128 * 4];
   __shared__ int bq[64 * 4];
   __shared__ int qk[LS == FDTBX_LINESHAPE_HOSEMANN ? 128 * 4 : 1];  // node indices (support edge)
   const int wv = (int)(threadIdx.x >> 6);
@@ -92,7 +94,8 @@ __global__ void __launch_bounds__(256) k_profile_adj_units(ProfParams q, const f
     const int t = unit_range(q, T, offsets, u, U, &p0, &p1);
     if (t < 0) return;
     adjoint_range<LS>(q, refl, nodes, pix, tile, idx, grad_image, n_hkl, sums, partials, t, p0, p1, 64, qn + 128 * wv,
-                      qd + 128 * wv, bq + 64 * wv, LS == FDTBX_LINESHAPE_HOSEMANN ? qk + 128 * wv : nullptr);
+                      qd + 128 * wv, bq + 64 * wv, gw + 128 * wv,
+                      LS == FDTBX_LINESHAPE_HOSEMANN ? qk + 128 * wv : nullptr);
   });
 }
 
@@ -398,6 +401,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_
                                                       unsigned long long* __restrict__ counter) {
   __shared__ float4 qn[128];
   __shared__ float2 qd[128];
+  __shared__ __align__(16) float gw[128];
   __shared__ int bq[64];
   __shared__ int qk[128];  // node indices of the queue (the Hosemann support edge)
   for (;;) {
@@ -420,14 +424,14 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_
     float* pt = partials ? partials + 12 * e.pair_off : nullptr;
     switch (q.lineshape) {  // uniform across the wave
       case FDTBX_LINESHAPE_GAUSSIAN:
-        adjoint_tile<FDTBX_LINESHAPE_GAUSSIAN, 1, true>(q, rf, nd, px, tb, rp, ix, gi, e.n_hkl, sm, pt, t, qn, qd, bq);
+        adjoint_tile<FDTBX_LINESHAPE_GAUSSIAN, 1, true>(q, rf, nd, px, tb, rp, ix, gi, e.n_hkl, sm, pt, t, qn, qd, bq, gw);
         break;
       case FDTBX_LINESHAPE_HOSEMANN:
         adjoint_tile<FDTBX_LINESHAPE_HOSEMANN, 1, true>(q, rf, nd, px, tb, rp, ix, gi, e.n_hkl, sm, pt, t, qn, qd, bq,
-                                                        qk);
+                                                        gw, qk);
         break;
       default:
-        adjoint_tile<FDTBX_LINESHAPE_LAUE, 1, true>(q, rf, nd, px, tb, rp, ix, gi, e.n_hkl, sm, pt, t, qn, qd, bq);
+        adjoint_tile<FDTBX_LINESHAPE_LAUE, 1, true>(q, rf, nd, px, tb, rp, ix, gi, e.n_hkl, sm, pt, t, qn, qd, bq, gw);
     }
   }
 }
