@@ -735,6 +735,23 @@ int fdtbx_batch_profile_stacked(const fdtbx_batch_entry* entries, int32_t n_mode
                                 const double* pix, const double* tile, const double* stile, const int64_t* srowptr,
                                 const int32_t* sidx, float* image, int64_t* counter, void* stream);
 
+/* fdtbx_batch_profile_units: fdtbx_batch_profile_stacked with every item's list cut into units of
+ * at most unit_pairs pairs, one wave each, so that a list much longer than the others does not
+ * run as one wave at the end.  Each unit writes its 128 pixel sums to its own slot and a second
+ * kernel adds an item's units in order: the image is the same on every run, and agrees with
+ * fdtbx_batch_profile_stacked's to float32 rounding.  The items must cover every launched stacked
+ * tile; the caller builds, once, from the lists it uploads:
+ *   unit_ptr   device int64 [n_items + 1]: the first unit of each item, ceil(list length /
+ *              unit_pairs) units per item, n_units in all
+ *   unit_item  device int32 [n_units]: the item of each unit
+ *   partials   device float32 [n_units][128] scratch
+ * Does not allocate, copy to the host or synchronise. */
+int fdtbx_batch_profile_units(const fdtbx_batch_entry* entries, int32_t n_models, const int64_t* stack_off,
+                              const int64_t* stack_items, int64_t n_items, const int64_t* unit_ptr,
+                              const int32_t* unit_item, int64_t n_units, int64_t unit_pairs, const float* refl,
+                              const float* nodes, const double* pix, const double* tile, const double* stile,
+                              const int64_t* srowptr, const int32_t* sidx, float* image, float* partials, void* stream);
+
 /* Backward step for all models, after fdtbx_batch_forward with the same inputs:
  * grad_image (float32, laid out as the images) -> atom gradients (float32 [sum n_atoms]
  * each), d_globals (float64 [n_models][FDTBX_N_GLOBALS]) and dF2 (float32 [sum n_hkl]).  sums: device

@@ -12,7 +12,7 @@ the host and never synchronises, so it can be captured in a HIP graph
 Each model's tiles run in its own shape (its geometry's tile_w); ``autotune.tune_batch``
 picks the shape of a whole batch by timing the batched forward in each candidate shape.
 The forward walks stacked tiles (two launched tile rows per wave, one culling list for
-both, fdtbx_batch_profile_stacked) unless the engine is built with stacked=False; the
+both, fdtbx_batch_profile_units) unless the engine is built with stacked=False; the
 backward walks the single tiles.
 """
 from __future__ import annotations
@@ -30,6 +30,15 @@ RB = 256  # reflections / atoms / node-table rows per block of the work tables
 
 def _pack(model: int, first: int) -> int:
     return (model << 40) | first
+
+
+def unit_pairs(n_pairs: int) -> int:
+    """Pairs per unit of the batched forward for n_pairs (stacked tile, reflection) pairs: few
+    enough to give a small batch 16,384 units (down to 4 pairs each), and at most 2^20 units
+    (besides one per item) of 512 bytes of sums.  Forward at 4, 16, 64, 256, 1024 pairs per unit:
+    95,460 pairs 0.30/0.55/1.4/4.1/- ms; 1.39 million 1.68/1.67/2.7/6.1/- ms; 11.2 million
+    10.9/8.7/9.7/14.0/- ms; 172 million -/-/118/125/143 ms; 465 million -/-/418/423/460 ms."""
+    return max(4, min(16, -(-n_pairs // (1 << 14))), -(-n_pairs // (1 << 20)))
 
 
 class StaleListsError(RuntimeError):
@@ -51,7 +60,7 @@ class BatchEngine:
         self.shapes = []
         off = dict(atom=0, hkl=0, pix=0, tile=0, rowptr=0, pair=0, node=0, ff=0)
         refl_blocks, model_rb, atom_blocks, node_blocks, items, costs = [], [], [], [], [], []
-        # the forward's stacked tiles (fdtbx_batch_profile_stacked): two launched tile rows per
+        # the forward's stacked tiles (fdtbx_batch_profile_units): two launched tile rows per
         # wave, one culling list for both (the backward keeps the per-tile lists)
         self.stacked = bool(stacked)
         sboxes, srowptrs, sidxs, s_items, s_costs, stack_off = [], [], [], [], [], []
@@ -146,8 +155,16 @@ class BatchEngine:
         order = np.argsort(-cost, kind="stable")
         self.items = dev(np.asarray(items, dtype=np.int64)[order], torch.int64)
         if self.stacked:
-            s_order = np.argsort(-np.concatenate(s_costs), kind="stable")
+            s_cost = np.concatenate(s_costs).astype(np.int64)
+            s_order = np.argsort(-s_cost, kind="stable")
             self.stack_items = dev(np.asarray(s_items, dtype=np.int64)[s_order], torch.int64)
+            # the items' lists in units of at most unit_pairs pairs (fdtbx_batch_profile_units)
+            self.unit_pairs = unit_pairs(int(s_cost.sum()))
+            n_units = -(-s_cost[s_order] // self.unit_pairs)
+            self.unit_ptr = dev(np.concatenate([[0], np.cumsum(n_units)]), torch.int64)
+            self.unit_item = dev(np.repeat(np.arange(n_units.shape[0]), n_units), torch.int32)
+            self.n_units = int(n_units.sum())
+            self.unit_sums = torch.empty((max(self.n_units, 1), 128), dtype=torch.float32, device=device)
             self.stack_off = dev(np.asarray(stack_off, dtype=np.int64), torch.int64)
             self.stile = torch.cat(sboxes).contiguous()
             self.srowptr = torch.cat(srowptrs).contiguous()
@@ -258,11 +275,12 @@ class BatchEngine:
             B._ptr(self.idx), B._ptr(self.F), B._ptr(self.F2), B._ptr(self.refl), B._ptr(self.nodes),
             B._ptr(self.image), B._ptr(self.counter), B._stream()))
         if self.stacked:
-            B._check(B.lib().fdtbx_batch_profile_stacked(
+            B._check(B.lib().fdtbx_batch_profile_units(
                 B._ptr(self.entries), self.n, B._ptr(self.stack_off), B._ptr(self.stack_items),
-                int(self.stack_items.shape[0]), B._ptr(self.refl), B._ptr(self.nodes), B._ptr(self.pix),
-                B._ptr(self.tile), B._ptr(self.stile), B._ptr(self.srowptr), B._ptr(self.sidx), B._ptr(self.image),
-                B._ptr(self.counter), B._stream()))
+                int(self.stack_items.shape[0]), B._ptr(self.unit_ptr), B._ptr(self.unit_item), self.n_units,
+                self.unit_pairs, B._ptr(self.refl), B._ptr(self.nodes), B._ptr(self.pix), B._ptr(self.tile),
+                B._ptr(self.stile), B._ptr(self.srowptr), B._ptr(self.sidx), B._ptr(self.image),
+                B._ptr(self.unit_sums), B._stream()))
         return self.image
 
     def backward(self, grad_image: torch.Tensor, atoms: bool = True):

@@ -184,6 +184,9 @@ _SIGS = {
                             [ctypes.c_void_p] * 18 + [ctypes.c_void_p]),
     "fdtbx_batch_profile_stacked": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p,
                                                    ctypes.c_int64] + [ctypes.c_void_p] * 10),
+    "fdtbx_batch_profile_units": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p,
+                                                 ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64,
+                                                 ctypes.c_int64] + [ctypes.c_void_p] * 10),
     "fdtbx_batch_backward": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_int64,
                                             ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p,
                                             ctypes.c_int64, ctypes.c_int64] + [ctypes.c_void_p] * 26 + [ctypes.c_void_p]),

@@ -93,7 +93,7 @@ __global__ void __launch_bounds__(256) k_profile_adj_units(ProfParams q, const f
     int64_t p0, p1;
     const int t = unit_range(q, T, offsets, u, U, &p0, &p1);
     if (t < 0) return;
-    adjoint_range<LS>(q, refl, nodes, pix, tile, idx, grad_image, n_hkl, sums, partials, t, p0, p1, 64, qn + 128 * wv,
+    adjoint_range<LS>(q, refl, nodes, pix, tile, idx, grad_image, n_hkl, sums, partials, t, p0, p1, 64, 64, qn + 128 * wv,
                       qd + 128 * wv, bq + 64 * wv, gw + 128 * wv,
                       LS == FDTBX_LINESHAPE_HOSEMANN ? qk + 128 * wv : nullptr);
   });
@@ -392,47 +392,56 @@ static void recip_basis(const fdtbx_cell* cell, double* as) {
 }
 
 // ---------------------------------------------------------------- batched models
+// One wave per (model, tile) item and part of its list: part p takes the chunks p, p + parts, ... of
+// `chunk` pairs.  The pairs' sums go out on their own, so the parts need no combining, and the
+// longest lists (50 times the mean in a batch of ragged models) no longer run as one wave, which
+// took 129 ms of a backward's 336 (32 models, 49,920 items) and all of 5.7 ms (6 models of up to
+// 128 x 128 pixels, 768 items).  A launch of fewer than kAdjFewItems items is cut finer, as it would
+// not fill the card: 64 parts of 4 pairs against 16 of 16 take 0.46 against 0.80 ms for 768 items
+// and 3.0 against 3.3 for 6,272, but 18.6 against 16.5 for 17,728 and 304 against 265 for 49,920
+// (a set-up that fills 4 of 64 lanes).  Four waves in a workgroup ran 3 to 9% slower than one.
+constexpr int64_t kAdjFewItems = 8192;
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_b_profile_adj(const fdtbx_batch_entry* __restrict__ ent, const int64_t* __restrict__ items,
-                                                      int64_t n_items, const float* __restrict__ refl,
+                                                      int parts, int chunk, const float* __restrict__ refl,
                                                       const float* __restrict__ nodes, const double* __restrict__ pix,
                                                       const double* __restrict__ tile, const int64_t* __restrict__ rowptr,
                                                       const int32_t* __restrict__ idx, const float* __restrict__ grad_image,
-                                                      double* __restrict__ sums, float* __restrict__ partials,
-                                                      unsigned long long* __restrict__ counter) {
+                                                      double* __restrict__ sums, float* __restrict__ partials) {
   __shared__ float4 qn[128];
   __shared__ float2 qd[128];
   __shared__ __align__(16) float gw[128];
   __shared__ int bq[64];
   __shared__ int qk[128];  // node indices of the queue (the Hosemann support edge)
-  for (;;) {
-    const int64_t it = next_item(counter);
-    if (it >= n_items) break;
-    const int64_t packed = items[it];
-    const int m = (int)(packed >> 40);
-    const int t = (int)(packed & ((1ll << 40) - 1));
-    const fdtbx_batch_entry& e = ent[m];
-    ProfParams q;
-    prof_params(&e.model, &q);
-    const float* rf = refl + (int64_t)FDTBX_REFL_FLOATS * e.hkl_off;
-    const float* nd = nodes + (int64_t)FDTBX_NODE_FLOATS * e.node_off;
-    const double* px = pix + 2 * e.pix_off;
-    const double* tb = tile + 8 * e.tile_off;
-    const int64_t* rp = rowptr + e.rowptr_off;
-    const int32_t* ix = idx + e.pair_off;
-    const float* gi = grad_image + e.pix_off;
-    double* sm = sums + 6 * e.hkl_off;
-    float* pt = partials ? partials + 12 * e.pair_off : nullptr;
-    switch (q.lineshape) {  // uniform across the wave
-      case FDTBX_LINESHAPE_GAUSSIAN:
-        adjoint_tile<FDTBX_LINESHAPE_GAUSSIAN, 1, true>(q, rf, nd, px, tb, rp, ix, gi, e.n_hkl, sm, pt, t, qn, qd, bq, gw);
-        break;
-      case FDTBX_LINESHAPE_HOSEMANN:
-        adjoint_tile<FDTBX_LINESHAPE_HOSEMANN, 1, true>(q, rf, nd, px, tb, rp, ix, gi, e.n_hkl, sm, pt, t, qn, qd, bq,
-                                                        gw, qk);
-        break;
-      default:
-        adjoint_tile<FDTBX_LINESHAPE_LAUE, 1, true>(q, rf, nd, px, tb, rp, ix, gi, e.n_hkl, sm, pt, t, qn, qd, bq, gw);
-    }
+  const int part = (int)(blockIdx.x % (unsigned)parts);
+  const int64_t packed = items[blockIdx.x / (unsigned)parts];
+  const int m = (int)(packed >> 40);
+  const int t = (int)(packed & ((1ll << 40) - 1));
+  const fdtbx_batch_entry& e = ent[m];
+  ProfParams q;
+  prof_params(&e.model, &q);
+  const float* rf = refl + (int64_t)FDTBX_REFL_FLOATS * e.hkl_off;
+  const float* nd = nodes + (int64_t)FDTBX_NODE_FLOATS * e.node_off;
+  const double* px = pix + 2 * e.pix_off;
+  const double* tb = tile + 8 * e.tile_off;
+  const int64_t* rp = rowptr + e.rowptr_off;
+  const int32_t* ix = idx + e.pair_off;
+  const float* gi = grad_image + e.pix_off;
+  double* sm = sums + 6 * e.hkl_off;
+  float* pt = partials ? partials + 12 * e.pair_off : nullptr;
+  const int64_t p0 = rp[t] + (int64_t)chunk * part, p1 = rp[t + 1], step = (int64_t)chunk * parts;
+  if (p0 >= p1) return;  // uniform
+  switch (q.lineshape) {  // uniform across the wave
+    case FDTBX_LINESHAPE_GAUSSIAN:
+      adjoint_range<FDTBX_LINESHAPE_GAUSSIAN, true>(q, rf, nd, px, tb, ix, gi, e.n_hkl, sm, pt, t, p0, p1, step,
+                                                    chunk, qn, qd, bq, gw);
+      break;
+    case FDTBX_LINESHAPE_HOSEMANN:
+      adjoint_range<FDTBX_LINESHAPE_HOSEMANN, true>(q, rf, nd, px, tb, ix, gi, e.n_hkl, sm, pt, t, p0, p1, step,
+                                                    chunk, qn, qd, bq, gw, qk);
+      break;
+    default:
+      adjoint_range<FDTBX_LINESHAPE_LAUE, true>(q, rf, nd, px, tb, ix, gi, e.n_hkl, sm, pt, t, p0, p1, step,
+                                                chunk, qn, qd, bq, gw);
   }
 }
 
@@ -567,7 +576,6 @@ __global__ void k_b_set_globals(fdtbx_batch_entry* __restrict__ ent, int32_t n_m
   ent[m].stale = stale;
 }
 
-static constexpr unsigned kPersistentBlocksAdj = 8192;
 
 }  // namespace fdtbx
 
@@ -598,12 +606,11 @@ int launch_batch_backward(const fdtbx_batch_entry* ent, int32_t n_models, const 
     hipLaunchKernelGGL(k_zero_f64, dim3((unsigned)ceil_div(6 * n_hkl_total, 256)), dim3(256), 0, s, sums, 6 * n_hkl_total);
     FDTBX_LAUNCH_CHECK("batch adjoint zero");
   }
-  hipLaunchKernelGGL(k_zero_f64, dim3(1), dim3(64), 0, s, (double*)counter, (int64_t)1);
-  FDTBX_LAUNCH_CHECK("batch adjoint counter");
+  if (n_items > INT32_MAX / 64) return fail(FDTBX_ERR_UNSUPPORTED, "batch backward: too many items");
   if (n_items > 0) {
-    unsigned nb = n_items < (int64_t)kPersistentBlocksAdj ? (unsigned)n_items : kPersistentBlocksAdj;
-    hipLaunchKernelGGL(k_b_profile_adj, dim3(nb), dim3(64), 0, s, ent, items, n_items, refl, nodes, pix, tile, rowptr, idx,
-                       grad_image, sums, fixed ? fixed->partials : nullptr, (unsigned long long*)counter);
+    const int parts = n_items < kAdjFewItems ? 64 : 16, chunk = n_items < kAdjFewItems ? 4 : 16;
+    hipLaunchKernelGGL(k_b_profile_adj, dim3((unsigned)(n_items * parts)), dim3(64), 0, s, ent, items, parts, chunk, refl,
+                       nodes, pix, tile, rowptr, idx, grad_image, sums, fixed ? fixed->partials : nullptr);
     FDTBX_LAUNCH_CHECK("batch profile adjoint");
   }
   if (fixed && n_hkl_total > 0) {

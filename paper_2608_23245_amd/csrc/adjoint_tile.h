@@ -173,8 +173,8 @@ __device__ __forceinline__ void weighted_sums(const float* acc, float* red, cons
 // twelve float32 sums (r's six, then the mate's six; zero without the up-down fold) at
 // partials[12 p], for a reduction in a fixed order (fdtbx_pair_reduce).
 //
-// adjoint_range walks the chunks of 64 pairs of tile t's list that start at from, from + step,
-// ... below p1, with this wave's queues qn, qd, bq; adjoint_tile gives each of its WAVES waves
+// adjoint_range walks the chunks of `chunk` (at most 64) pairs of tile t's list that start at from,
+// from + step, ... below p1, with this wave's queues qn, qd, bq; adjoint_tile gives each of its WAVES waves
 // its share of the list, and the balanced launch gives a wave one unit of the list at a time.
 template <int LS, bool PRE = false>
 __device__ __forceinline__ void adjoint_range(const ProfParams& q, const float* __restrict__ refl,
@@ -182,7 +182,8 @@ __device__ __forceinline__ void adjoint_range(const ProfParams& q, const float* 
                                               const double* __restrict__ tile, const int32_t* __restrict__ idx,
                                               const float* __restrict__ grad_image, int64_t n_hkl,
                                               double* __restrict__ sums, float* __restrict__ partials, const int t,
-                                              int64_t from, int64_t p1, int64_t step, float4* qn, float2* qd, int* bq,
+                                              int64_t from, int64_t p1, int64_t step, int chunk, float4* qn,
+                                              float2* qd, int* bq,
                                               float* gw, int* qk = nullptr) {
   const int lane = threadIdx.x & 63;
   constexpr bool EDGE = LS == FDTBX_LINESHAPE_HOSEMANN;
@@ -212,7 +213,7 @@ __device__ __forceinline__ void adjoint_range(const ProfParams& q, const float* 
     int w01 = 0, w23 = 0;
     float lol[3] = {0.f, 0.f, 0.f}, hil[3] = {0.f, 0.f, 0.f};
     bool ok = false;
-    if (base + lane < p1) {
+    if (lane < chunk && base + lane < p1) {
       rl = idx[base + lane];
       ok = pair_setup<PRE>(q, refl + (int64_t)FDTBX_REFL_FLOATS * rl, nodes, box, &w01, &w23, lol, hil);
     }
@@ -301,7 +302,7 @@ __device__ __forceinline__ void adjoint_tile(const ProfParams& q, const float* _
                                              float* gw, int* qk = nullptr) {
   const int wv = WAVES > 1 ? (int)(threadIdx.x >> 6) : 0;
   adjoint_range<LS, PRE>(q, refl, nodes, pix, tile, idx, grad_image, n_hkl, sums, partials, t, offsets[t] + 64 * wv,
-                    offsets[t + 1], 64 * WAVES, qn + 128 * wv, qd + 128 * wv, bq + 64 * wv, gw + 128 * wv,
+                    offsets[t + 1], 64 * WAVES, 64, qn + 128 * wv, qd + 128 * wv, bq + 64 * wv, gw + 128 * wv,
                     qk ? qk + 128 * wv : nullptr);
 }
 

@@ -540,6 +540,22 @@ extern "C" int fdtbx_batch_forward(const fdtbx_batch_entry* entries, int32_t n_m
   return launch_batch_profile(entries, tile_items, n_items, refl, nodes, pix, tile, rowptr, idx, image, counter, s);
 }
 
+extern "C" int fdtbx_batch_profile_units(const fdtbx_batch_entry* entries, int32_t n_models, const int64_t* stack_off,
+                                         const int64_t* stack_items, int64_t n_items, const int64_t* unit_ptr,
+                                         const int32_t* unit_item, int64_t n_units, int64_t unit_pairs,
+                                         const float* refl, const float* nodes, const double* pix, const double* tile,
+                                         const double* stile, const int64_t* srowptr, const int32_t* sidx, float* image,
+                                         float* partials, void* stream) {
+  if (!entries || n_models <= 0 || n_items < 0 || n_units < 0 || unit_pairs < 1)
+    return fail(FDTBX_ERR_INVALID_ARGUMENT, "bad sizes");
+  if (!stack_off || !stack_items || !unit_ptr || !unit_item || !refl || !nodes || !pix || !tile || !stile || !srowptr ||
+      !sidx || !image || !partials)
+    return fail(FDTBX_ERR_INVALID_ARGUMENT, "null pointer");
+  if (n_items > INT32_MAX || n_units > INT32_MAX) return fail(FDTBX_ERR_UNSUPPORTED, "more than 2^31 items or units");
+  return launch_batch_profile_units(entries, stack_off, stack_items, n_items, unit_ptr, unit_item, n_units, unit_pairs,
+                                    refl, nodes, pix, tile, stile, srowptr, sidx, image, partials, (hipStream_t)stream);
+}
+
 extern "C" int fdtbx_batch_profile_stacked(const fdtbx_batch_entry* entries, int32_t n_models, const int64_t* stack_off,
                                            const int64_t* stack_items, int64_t n_items, const float* refl,
                                            const float* nodes, const double* pix, const double* tile,

@@ -64,14 +64,16 @@ __host__ __device__ inline int64_t node_rows(int64_t n) {
   return n * n + nb * nb;
 }
 
-// Next item of a persistent launch: lane 0 takes it from the counter and the wave reads
-// lane 0's value into scalar registers (so everything indexed by it is loaded as uniform).
-__device__ inline int64_t next_item(unsigned long long* counter) {
+// Next item of a persistent launch over n items whose workgroup b starts with item b: none when
+// the launch has a workgroup for every item, else lane 0 takes it from the counter and the wave
+// reads lane 0's value into scalar registers (so everything indexed by it is loaded as uniform).
+__device__ inline int64_t next_item(unsigned long long* counter, int64_t n) {
+  if ((int64_t)gridDim.x >= n) return n;
   unsigned long long mine = 0;
   if ((threadIdx.x & 63) == 0) mine = atomicAdd(counter, 1ull);
   const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)mine);
   const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(mine >> 32));
-  return (int64_t)(((unsigned long long)hi << 32) | lo);
+  return (int64_t)(((unsigned long long)hi << 32) | lo) + gridDim.x;
 }
 
 // Orders one wave's LDS accesses before and after this point (what __syncthreads does for a
@@ -227,6 +229,11 @@ int launch_batch_profile_stacked(const fdtbx_batch_entry* ent, const int64_t* so
                                  int64_t n_items, const float* refl, const float* nodes, const double* pix,
                                  const double* tile, const double* stile, const int64_t* srowptr, const int32_t* sidx,
                                  float* image, int64_t* counter, hipStream_t s);
+int launch_batch_profile_units(const fdtbx_batch_entry* ent, const int64_t* soff, const int64_t* items,
+                               int64_t n_items, const int64_t* unit_ptr, const int32_t* unit_item, int64_t n_units,
+                               int64_t unit_pairs, const float* refl, const float* nodes, const double* pix,
+                               const double* tile, const double* stile, const int64_t* srowptr, const int32_t* sidx,
+                               float* image, float* partials, hipStream_t s);
 // Fixed-order accumulation of the adjoint sums (fdtbx_pair_reduce): per-pair partials
 // float32 [n_pairs][12] and the pairs of each reflection in a fixed order.
 struct PairOrder {

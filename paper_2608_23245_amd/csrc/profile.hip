@@ -82,9 +82,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) k_
   __shared__ float4 qn[128];
   __shared__ int bq[64];
   __shared__ int qk[128];  // node indices of the queue (the Hosemann support edge)
-  for (;;) {
-    const int64_t it = next_item(counter);
-    if (it >= n_items) break;
+  for (int64_t it = blockIdx.x; it < n_items; it = next_item(counter, n_items)) {
     const int64_t packed = items[it];
     const int m = (int)(packed >> 40);
     const int t = (int)(packed & ((1ll << 40) - 1));
@@ -185,9 +183,10 @@ __global__ void __launch_bounds__(64) k_unit_reduce(ProfParams q, UnitTable T, c
   const TilePixel px = tile_pixel(q, pix, tile, t, lane);
   const int64_t U = T.meta[1];
   const int64_t n = U > 0 ? ceil_div_dev(offsets[t + 1] - offsets[t], U) : 0, s = T.qscan[queue_pos(b, T.nj)];
+  const int64_t n_in = s < 0 ? 0 : (s + n < T.max_units ? n : T.max_units - s);  // within the capacity
   float acc = 0.0f;
-  for (int64_t k = 0; k < n && s + k < T.max_units; ++k)
-    if (s + k >= 0) acc += partials[(s + k) * 64 + lane];
+#pragma unroll 8
+  for (int64_t k = 0; k < n_in; ++k) acc += partials[(s + k) * 64 + lane];  // a tile of few pairs each has many units
   if (!px.in) return;
   write_folded(q, image, px.i, px.j, px.tx, px.ty, (float)(q.delta / (px.R + q.delta)) * acc);
 }
@@ -211,72 +210,160 @@ int launch_batch_profile(const fdtbx_batch_entry* ent, const int64_t* items, int
   return FDTBX_OK;
 }
 
-// Batched models on stacked tiles: every wave takes (model, stacked tile) items as k_b_profile
-// takes tiles.  Stacked tile s = sy tiles_x + sx holds tile rows 2 sy and 2 sy + 1 (the second
-// when it is launched) of tile column sx; its box, row pointers and list start at the model's
-// offsets in soff ([m][3]: first box, first row pointer, first list entry; the row pointers are
-// relative to the model's first list entry).
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_b_profile_stacked(const fdtbx_batch_entry* __restrict__ ent,
-                                                          const int64_t* __restrict__ soff,
-                                                          const int64_t* __restrict__ items, int64_t n_items,
-                                                          const float* __restrict__ refl,
-                                                          const float* __restrict__ nodes,
-                                                          const double* __restrict__ pix,
-                                                          const double* __restrict__ tile,
-                                                          const double* __restrict__ stile,
-                                                          const int64_t* __restrict__ srowptr,
-                                                          const int32_t* __restrict__ sidx, float* __restrict__ image,
-                                                          unsigned long long* __restrict__ counter) {
+// ---------------------------------------------------------------- batched models on stacked tiles
+// Stacked tile s = sy tiles_x + sx holds tile rows 2 sy and 2 sy + 1 (the second when it is
+// launched) of tile column sx; its box, row pointers and list start at the model's offsets in soff
+// ([m][3]: first box, first row pointer, first list entry; the row pointers are relative to the
+// model's first list entry).
+struct StackedItem {
+  ProfParams q;
+  TilePixel a, b;  // the lane's pixels of the two tiles (b far from every reflection if there is one)
+  TileBox box;
+  const float *rf, *nd;
+  const int32_t* ix;
+  float* im;
+  int64_t p0, p1;  // the stacked tile's list
+};
+
+__device__ __forceinline__ void stacked_item(const fdtbx_batch_entry* __restrict__ ent,
+                                             const int64_t* __restrict__ soff, int64_t packed,
+                                             const float* __restrict__ refl, const float* __restrict__ nodes,
+                                             const double* __restrict__ pix, const double* __restrict__ tile,
+                                             const double* __restrict__ stile, const int64_t* __restrict__ srowptr,
+                                             const int32_t* __restrict__ sidx, float* __restrict__ image,
+                                             StackedItem& it) {
+  const int lane = threadIdx.x & 63;
+  const int m = (int)(packed >> 40);
+  const int st = (int)(packed & ((1ll << 40) - 1));
+  const fdtbx_batch_entry& e = ent[m];
+  prof_params(&e.model, &it.q);
+  const double* px = pix + 2 * e.pix_off;
+  const double* tb = tile + 8 * e.tile_off;
+  const double* sbox = stile + 8 * (soff[3 * m] + st);
+  const int64_t* rp = srowptr + soff[3 * m + 1];
+  it.ix = sidx + soff[3 * m + 2];
+  it.im = image + e.pix_off;
+  const int sx = st % it.q.tiles_x, sy = st / it.q.tiles_x;
+  const int ta = 2 * sy * it.q.tiles_x + sx;
+  const bool two = 2 * sy + 1 < it.q.lrows;  // uniform
+  it.a = tile_pixel(it.q, px, tb, ta, lane);
+  it.b = tile_pixel(it.q, px, tb, two ? ta + it.q.tiles_x : ta, lane);
+  if (!two) {
+    it.b.in = false;
+    it.b.R = 1.0e30;
+    it.b.Z = 0.0;
+  }
+  it.box = {sbox[0], sbox[1], sbox[2], sbox[3]};
+  it.rf = refl + (int64_t)FDTBX_REFL_FLOATS * e.hkl_off;
+  it.nd = nodes + (int64_t)FDTBX_NODE_FLOATS * e.node_off;
+  it.p0 = rp[st];
+  it.p1 = rp[st + 1];
+}
+
+// The lane's two pixel sums over pairs p0 .. p1 of the item's list.
+__device__ __forceinline__ void stacked_sums(const StackedItem& it, int64_t p0, int64_t p1, float4* qn, int* bq,
+                                             int* qk, float* sa, float* sb) {
+  switch (it.q.lineshape) {  // uniform across the wave
+    case FDTBX_LINESHAPE_GAUSSIAN:
+      pairs_sum_stacked<FDTBX_LINESHAPE_GAUSSIAN>(it.q, it.rf, it.nd, it.ix, it.box, it.a.R, it.a.Z, it.b.R, it.b.Z, p0,
+                                                  p1, qn, bq, sa, sb);
+      break;
+    case FDTBX_LINESHAPE_HOSEMANN:
+      pairs_sum_stacked<FDTBX_LINESHAPE_HOSEMANN>(it.q, it.rf, it.nd, it.ix, it.box, it.a.R, it.a.Z, it.b.R, it.b.Z, p0,
+                                                  p1, qn, bq, sa, sb, qk);
+      break;
+    default:
+      pairs_sum_stacked<FDTBX_LINESHAPE_LAUE>(it.q, it.rf, it.nd, it.ix, it.box, it.a.R, it.a.Z, it.b.R, it.b.Z, p0, p1,
+                                              qn, bq, sa, sb);
+  }
+}
+
+// The item's pixels from their sums, with the Lorentz factor and the mirror folds.
+__device__ __forceinline__ void stacked_write(const StackedItem& it, float sa, float sb) {
+  const TilePixel &a = it.a, &b = it.b;
+  if (a.in) write_folded(it.q, it.im, a.i, a.j, a.tx, a.ty, (float)(it.q.delta / (a.R + it.q.delta)) * sa);
+  if (b.in) write_folded(it.q, it.im, b.i, b.j, b.tx, b.ty, (float)(it.q.delta / (b.R + it.q.delta)) * sb);
+}
+
+// Every wave takes (model, stacked tile) items as k_b_profile takes tiles.
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_b_profile_stacked(
+    const fdtbx_batch_entry* __restrict__ ent, const int64_t* __restrict__ soff, const int64_t* __restrict__ items,
+    int64_t n_items, const float* __restrict__ refl, const float* __restrict__ nodes, const double* __restrict__ pix,
+    const double* __restrict__ tile, const double* __restrict__ stile, const int64_t* __restrict__ srowptr,
+    const int32_t* __restrict__ sidx, float* __restrict__ image, unsigned long long* __restrict__ counter) {
   __shared__ float4 qn[128];
   __shared__ int bq[64];
   __shared__ int qk[128];  // node indices of the queue (the Hosemann support edge)
-  const int lane = threadIdx.x & 63;
-  for (;;) {
-    const int64_t it = next_item(counter);
-    if (it >= n_items) break;
-    const int64_t packed = items[it];
-    const int m = (int)(packed >> 40);
-    const int st = (int)(packed & ((1ll << 40) - 1));
-    const fdtbx_batch_entry& e = ent[m];
-    ProfParams q;
-    prof_params(&e.model, &q);
-    const double* px = pix + 2 * e.pix_off;
-    const double* tb = tile + 8 * e.tile_off;
-    const double* sbox = stile + 8 * (soff[3 * m] + st);
-    const int64_t* rp = srowptr + soff[3 * m + 1];
-    const int32_t* ix = sidx + soff[3 * m + 2];
-    float* im = image + e.pix_off;
-    const int sx = st % q.tiles_x, sy = st / q.tiles_x;
-    const int ta = 2 * sy * q.tiles_x + sx;
-    const bool two = 2 * sy + 1 < q.lrows;  // uniform
-    const TilePixel pa = tile_pixel(q, px, tb, ta, lane);
-    TilePixel pb = tile_pixel(q, px, tb, two ? ta + q.tiles_x : ta, lane);
-    if (!two) {
-      pb.in = false;
-      pb.R = 1.0e30;
-      pb.Z = 0.0;
-    }
-    const TileBox box = {sbox[0], sbox[1], sbox[2], sbox[3]};
-    const float* rf = refl + (int64_t)FDTBX_REFL_FLOATS * e.hkl_off;
-    const float* nd = nodes + (int64_t)FDTBX_NODE_FLOATS * e.node_off;
-    const int64_t p0 = rp[st], p1 = rp[st + 1];
+  for (int64_t k = blockIdx.x; k < n_items; k = next_item(counter, n_items)) {
+    StackedItem it;
+    stacked_item(ent, soff, items[k], refl, nodes, pix, tile, stile, srowptr, sidx, image, it);
     float sa = 0.0f, sb = 0.0f;
-    switch (q.lineshape) {  // uniform across the wave
-      case FDTBX_LINESHAPE_GAUSSIAN:
-        pairs_sum_stacked<FDTBX_LINESHAPE_GAUSSIAN>(q, rf, nd, ix, box, pa.R, pa.Z, pb.R, pb.Z, p0, p1, qn, bq, &sa,
-                                                    &sb);
-        break;
-      case FDTBX_LINESHAPE_HOSEMANN:
-        pairs_sum_stacked<FDTBX_LINESHAPE_HOSEMANN>(q, rf, nd, ix, box, pa.R, pa.Z, pb.R, pb.Z, p0, p1, qn, bq, &sa,
-                                                    &sb, qk);
-        break;
-      default:
-        pairs_sum_stacked<FDTBX_LINESHAPE_LAUE>(q, rf, nd, ix, box, pa.R, pa.Z, pb.R, pb.Z, p0, p1, qn, bq, &sa,
-                                                &sb);
-    }
-    if (pa.in) write_folded(q, im, pa.i, pa.j, pa.tx, pa.ty, (float)(q.delta / (pa.R + q.delta)) * sa);
-    if (pb.in) write_folded(q, im, pb.i, pb.j, pb.tx, pb.ty, (float)(q.delta / (pb.R + q.delta)) * sb);
+    stacked_sums(it, it.p0, it.p1, qn, bq, qk, &sa, &sb);
+    stacked_write(it, sa, sb);
   }
+}
+
+// The same items cut into units of at most U pairs, one wave each: unit u is the
+// (u - unit_ptr[k])-th of item k = unit_item[u] and writes its 128 pixel sums to a slot of its
+// own; k_b_unit_reduce adds an item's units in their order.  A list longer than the others (a
+// large model's tiles beside the beam hold 50 times the mean) then runs on many waves: with one
+// wave per item the longest list took 120 ms, nearly half of a forward of 32 models.
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_b_profile_units(
+    const fdtbx_batch_entry* __restrict__ ent, const int64_t* __restrict__ soff, const int64_t* __restrict__ items,
+    const int64_t* __restrict__ unit_ptr, const int32_t* __restrict__ unit_item, int64_t U,
+    const float* __restrict__ refl, const float* __restrict__ nodes, const double* __restrict__ pix,
+    const double* __restrict__ tile, const double* __restrict__ stile, const int64_t* __restrict__ srowptr,
+    const int32_t* __restrict__ sidx, float* __restrict__ image, float* __restrict__ partials) {
+  __shared__ float4 qn[128];
+  __shared__ int bq[64];
+  __shared__ int qk[128];  // node indices of the queue (the Hosemann support edge)
+  const int64_t u = blockIdx.x;
+  const int k = unit_item[u];
+  StackedItem it;
+  stacked_item(ent, soff, items[k], refl, nodes, pix, tile, stile, srowptr, sidx, image, it);
+  const int64_t p0 = it.p0 + (u - unit_ptr[k]) * U, p1 = p0 + U < it.p1 ? p0 + U : it.p1;
+  float sa = 0.0f, sb = 0.0f;
+  stacked_sums(it, p0, p1, qn, bq, qk, &sa, &sb);
+  float* const o = partials + 128 * u + (threadIdx.x & 63);
+  o[0] = sa;
+  o[64] = sb;
+}
+
+__global__ void __launch_bounds__(64) k_b_unit_reduce(
+    const fdtbx_batch_entry* __restrict__ ent, const int64_t* __restrict__ soff, const int64_t* __restrict__ items,
+    const int64_t* __restrict__ unit_ptr, const double* __restrict__ pix, const double* __restrict__ tile,
+    const double* __restrict__ stile, const int64_t* __restrict__ srowptr, float* __restrict__ image,
+    const float* __restrict__ partials) {
+  const int64_t k = blockIdx.x;
+  StackedItem it;
+  stacked_item(ent, soff, items[k], nullptr, nullptr, pix, tile, stile, srowptr, nullptr, image, it);
+  float sa = 0.0f, sb = 0.0f;
+  const int64_t u1 = unit_ptr[k + 1];
+#pragma unroll 8
+  for (int64_t u = unit_ptr[k]; u < u1; ++u) {
+    const float* const o = partials + 128 * u + (threadIdx.x & 63);
+    sa += o[0];
+    sb += o[64];
+  }
+  stacked_write(it, sa, sb);
+}
+
+int launch_batch_profile_units(const fdtbx_batch_entry* ent, const int64_t* soff, const int64_t* items,
+                               int64_t n_items, const int64_t* unit_ptr, const int32_t* unit_item, int64_t n_units,
+                               int64_t unit_pairs, const float* refl, const float* nodes, const double* pix,
+                               const double* tile, const double* stile, const int64_t* srowptr, const int32_t* sidx,
+                               float* image, float* partials, hipStream_t s) {
+  if (n_units > 0) {
+    hipLaunchKernelGGL(k_b_profile_units, dim3((unsigned)n_units), dim3(64), 0, s, ent, soff, items, unit_ptr, unit_item,
+                       unit_pairs, refl, nodes, pix, tile, stile, srowptr, sidx, image, partials);
+    FDTBX_LAUNCH_CHECK("batch profile units");
+  }
+  if (n_items > 0) {
+    hipLaunchKernelGGL(k_b_unit_reduce, dim3((unsigned)n_items), dim3(64), 0, s, ent, soff, items, unit_ptr, pix, tile,
+                       stile, srowptr, image, (const float*)partials);
+    FDTBX_LAUNCH_CHECK("batch profile unit sums");
+  }
+  return FDTBX_OK;
 }
 
 int launch_batch_profile_stacked(const fdtbx_batch_entry* ent, const int64_t* soff, const int64_t* items,

@@ -302,8 +302,12 @@ __device__ __forceinline__ float pairs_sum(const ProfParams& q, const float* __r
   static_assert(!(SPLIT && COUNT), "the counting pass tests every node");
   constexpr bool EDGE = LS == FDTBX_LINESHAPE_HOSEMANN && !COUNT;
   const int lane = threadIdx.x & 63;
-  float acc = 0.0f;
+  float acc = 0.0f, total = 0.0f;
   for (int64_t base = from; base < p1; base += step) {
+    if (PRE) {  // the batched launch's whole lists: a block sum per chunk keeps long sums accurate
+      total += acc;
+      acc = 0.0f;
+    }
     int32_t rl = 0;
     int w01 = 0, w23 = 0;
     float lol[3] = {0.f, 0.f, 0.f}, hil[3] = {0.f, 0.f, 0.f}, fll[3] = {0.f, 0.f, 0.f}, fhl[3] = {0.f, 0.f, 0.f};
@@ -367,7 +371,7 @@ __device__ __forceinline__ float pairs_sum(const ProfParams& q, const float* __r
       if (!COUNT) acc = fmaf(f.at(RS_WK), accr, acc);
     }
   }
-  return acc;
+  return PRE ? total + acc : acc;
 }
 
 // The walk of walk_queue for a lane holding two pixels (al, bl: their tagged alpha): each

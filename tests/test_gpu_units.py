@@ -61,3 +61,58 @@ def test_units_around_the_number_of_waves(crop, total):
     assert (img - ref).abs().max().item() <= 2e-6 * scale
     s = want.abs().amax(dim=0).clamp(min=1e-300)
     assert ((sums - want).abs() / s).max().item() <= 1e-10
+
+
+def batch_of(shapes, **kw):
+    from paper_2608_23245_amd.batch import BatchEngine
+    wls = [W.small(90 + i, width=w, height=h, center=(w / 2, h / 2), sigma_theta=0.05, gamma_theta=0.02, n_nodes=10, **kw)
+           for i, (w, h) in enumerate(shapes)]
+    return wls, BatchEngine(wls)
+
+
+@pytest.mark.parametrize("unit", [1, 3, 64, 65, 100000])
+def test_batch_units_match_whole_lists(unit):
+    """The batched forward in units of one pair up to more than the longest list, lists of an odd
+    number of tile rows and of none among them, against the launch with one wave per list: the
+    same terms grouped otherwise (2e-6 of each model's largest value)."""
+    _, eng = batch_of([(40, 37), (17, 9), (64, 64)])
+    print(f"batch units of {unit}", flush=True)
+    eng.forward()
+    lens = np.zeros(int(eng.stack_items.shape[0]), dtype=np.int64)
+    off, rp = eng.stack_off.cpu().numpy().reshape(-1, 3), eng.srowptr.cpu().numpy()
+    for k, packed in enumerate(eng.stack_items.cpu().numpy()):
+        m, s = int(packed >> 40), int(packed & ((1 << 40) - 1))
+        lens[k] = rp[off[m, 1] + s + 1] - rp[off[m, 1] + s]
+    n = -(-lens // unit)
+    ptr = torch.as_tensor(np.concatenate([[0], np.cumsum(n)]), dtype=torch.int64).cuda()
+    item = torch.as_tensor(np.repeat(np.arange(n.shape[0]), n), dtype=torch.int32).cuda()
+    sums = torch.full((max(int(n.sum()), 1), 128), float("nan"), device="cuda")
+    got, want = torch.full_like(eng.image, 7.0), torch.full_like(eng.image, 9.0)
+    p = B._ptr
+    tail = (p(eng.refl), p(eng.nodes), p(eng.pix), p(eng.tile), p(eng.stile), p(eng.srowptr), p(eng.sidx))
+    head = (p(eng.entries), eng.n, p(eng.stack_off), p(eng.stack_items), int(eng.stack_items.shape[0]))
+    B._check(B.lib().fdtbx_batch_profile_units(*head, p(ptr), p(item), int(n.sum()), unit, *tail, p(got), p(sums),
+                                               B._stream()))
+    B._check(B.lib().fdtbx_batch_profile_stacked(*head, *tail, p(want), p(eng.counter), B._stream()))
+    for m in range(eng.n):
+        s = slice(eng.pix_off[m], eng.pix_off[m + 1])
+        assert (got[s] - want[s]).abs().max().item() <= 2e-6 * want[s].abs().max().item()
+    assert B.lib().fdtbx_batch_profile_units(*head, p(ptr), p(item), int(n.sum()), 0, *tail, p(got), p(sums),
+                                             B._stream()) == -1
+
+
+@pytest.mark.parametrize("side", [88, 728])
+def test_batch_adjoint_parts(side):
+    """The batched adjoint with lists in 64 parts (121 tiles) and in 16 (8281 tiles) against the
+    single-model launch: every pair's sums are the same, added in another order (the single
+    launch's images are walked with wider node windows, which adds nothing but zeros)."""
+    wls, eng = batch_of([(side, side)], d_min=4.0, distance=60.0 * side / 24)
+    print(f"batch adjoint, {eng.items.shape[0]} items", flush=True)
+    eng.forward()
+    G = torch.as_tensor(np.random.default_rng(5).normal(size=side * side), dtype=torch.float32).cuda()
+    eng.backward(G)
+    model = eng.models[0]
+    off = eng.rowptr
+    want = B.profile_adjoint(model, eng.refl, eng.nodes, eng.pix, eng.tile, off, eng.idx, G.view(side, side))
+    s = want.abs().amax(dim=0).clamp(min=1e-300)
+    assert ((eng.sums - want).abs() / s).max().item() <= 1e-6
