@@ -80,24 +80,31 @@ __global__ void __launch_bounds__(kEnumThreads) k_enum_count(EnumParams p, int64
   if (threadIdx.x == 0) block_counts[blockIdx.x] = tot;
 }
 
-// Exclusive scan of n values in place with one block; writes the grand total to *total.
+// Exclusive scan of n values in place with one block; writes the grand total to *total.  Each
+// thread takes kScanPer consecutive values of a round (one value each took 20 us for 16,384: 16
+// rounds of four barriers).
+static constexpr int kScanPer = 8;
 __global__ void __launch_bounds__(1024) k_scan_inplace(int64_t* v, int64_t n, int64_t* total) {
   __shared__ int64_t lds[16];
-  __shared__ int64_t carry_s;
-  if (threadIdx.x == 0) carry_s = 0;
-  __syncthreads();
-  for (int64_t b = 0; b < n; b += blockDim.x) {
-    int64_t i = b + threadIdx.x;
-    int64_t x = i < n ? v[i] : 0;
+  int64_t carry = 0;  // the same in every thread
+  for (int64_t b = 0; b < n; b += (int64_t)blockDim.x * kScanPer) {
+    const int64_t i = b + (int64_t)threadIdx.x * kScanPer;
+    int64_t x[kScanPer], sum = 0;
+#pragma unroll
+    for (int k = 0; k < kScanPer; ++k) {
+      x[k] = i + k < n ? v[i + k] : 0;
+      sum += x[k];
+    }
     int64_t tot;
-    int64_t ex = block_exclusive_scan(x, lds, &tot);
-    int64_t carry = carry_s;
-    if (i < n) v[i] = carry + ex;
-    __syncthreads();
-    if (threadIdx.x == 0) carry_s = carry + tot;
-    __syncthreads();
+    int64_t at = carry + block_exclusive_scan(sum, lds, &tot);
+#pragma unroll
+    for (int k = 0; k < kScanPer; ++k) {
+      if (i + k < n) v[i + k] = at;
+      at += x[k];
+    }
+    carry += tot;
   }
-  if (threadIdx.x == 0) *total = carry_s;
+  if (threadIdx.x == 0) *total = carry;
 }
 
 __global__ void __launch_bounds__(kEnumThreads) k_enum_fill(EnumParams p, const int64_t* block_offsets, int32_t* out) {
@@ -509,19 +516,13 @@ struct CullParams {
   int64_t n_hkl, n_words;
 };
 
-// The exact predicate of the header.  box = tile box (8 doubles), c = culling record.
-__device__ static inline bool cull_test(const double* box, const double* c) {
-  if (!(c[12] != 0.0)) return false;
-  if (!(c[0] <= box[1] && box[0] <= c[1])) return false;
-  if (!(c[2] <= box[3] && box[2] <= c[3])) return false;
-  if (!(c[4] <= box[5] && box[4] <= c[5])) return false;
-  if (c[8] >= 0.0) {
-    double m1 = fmax(c[6] * box[0], c[6] * box[1]) + fmax(c[7] * box[2], c[7] * box[3]);
-    if (!(m1 >= -c[8])) return false;
-    double m2 = fmax(c[9] * box[0], c[9] * box[1]) + fmax(c[10] * box[2], c[10] * box[3]);
-    if (!(m2 >= -c[11])) return false;
-  }
-  return true;
+// The exact predicate of the header for a record that is kept, without branches.  box = tile box
+// (the first 6 doubles), c = culling record, wedge: c[8] >= 0.
+__device__ __forceinline__ bool cull_test_alive(const double* box, const double* c, bool wedge) {
+  const double m1 = fmax(c[6] * box[0], c[6] * box[1]) + fmax(c[7] * box[2], c[7] * box[3]);
+  const double m2 = fmax(c[9] * box[0], c[9] * box[1]) + fmax(c[10] * box[2], c[10] * box[3]);
+  return (c[0] <= box[1]) & (box[0] <= c[1]) & (c[2] <= box[3]) & (box[2] <= c[3]) & (c[4] <= box[5]) &
+         (box[4] <= c[5]) & (!wedge | ((m1 >= -c[8]) & (m2 >= -c[11])));
 }
 
 // Superblock boxes: union of the boxes of its tiles.
@@ -555,14 +556,18 @@ __global__ void __launch_bounds__(64) k_sb_mask(CullParams q, const double* __re
   bool have = r < q.n_hkl;
   for (int k = 0; k < 13; ++k) c[k] = have ? cull[FDTBX_CULL_DOUBLES * r + k] : 0.0;
   const int nsb = q.sb_x * q.sb_y, per = (nsb + (int)gridDim.y - 1) / (int)gridDim.y;
-  const int s1 = min(nsb, per * ((int)blockIdx.y + 1));
-  for (int s = per * (int)blockIdx.y; s < s1; ++s) {
-    if ((s % q.sb_x) * kSB >= q.lcols || (s / q.sb_x) * kSB >= q.lrows) continue;  // no tile of it gets a list
-    double box[6];
-    for (int k = 0; k < 6; ++k) box[k] = sb[8 * (int64_t)s + k];
-    bool hit = have && cull_test(box, c);
-    uint64_t m = __ballot(hit);
-    if (threadIdx.x == 0) mask[(int64_t)s * q.n_words + w] = m;
+  const int s0 = per * (int)blockIdx.y, s1 = min(nsb, s0 + per);
+  const bool alive = have && c[12] != 0.0, wedge = c[8] >= 0.0;
+  int sx = s0 % q.sb_x, sy = s0 / q.sb_x;
+  for (int s = s0; s < s1; ++s) {
+    if (sx * kSB < q.lcols && sy * kSB < q.lrows) {  // else no tile of it gets a list
+      const uint64_t m = __ballot(alive & cull_test_alive(sb + 8 * (int64_t)s, c, wedge));
+      if (threadIdx.x == 0) mask[(int64_t)s * q.n_words + w] = m;
+    }
+    if (++sx == q.sb_x) {
+      sx = 0;
+      ++sy;
+    }
   }
 }
 
@@ -576,6 +581,12 @@ __global__ void __launch_bounds__(64) k_sb_mask(CullParams q, const double* __re
 // plus the hits of the waves before w, so every list comes out ascending.  Tiles off the
 // detector or in a column the mirror fold does not launch get no list (NaN boxes fail every
 // test; their count is 0), and so do the rows the up-down fold does not launch.
+// Bound by the latency of the record reads and the binary64 tests of the heaviest superblocks
+// (one block each).  The loop over the tiles is rolled, its boxes read from LDS, and lane u keeps
+// tile u's count or position: unrolled over the sixteen tiles, with those in every lane's
+// registers, the kernels spilled 130 registers: count and fill 21 and 23 -> 7 and 8 us (64 tiles,
+// 150 reflections), 88 and 114 -> 20 and 20 us (10,100 tiles, 514), 1.15 and 1.48 -> 0.25 and 0.27 ms
+// (medium, both folds), 10.3 and 13.4 -> 2.2 and 2.1 ms (large, both folds).
 static constexpr int kWordsPer = 16;
 static constexpr int kTB = kSB * kSB;  // tiles and waves per block
 
@@ -588,7 +599,7 @@ __global__ void __launch_bounds__(64 * kTB) k_tile_lists(CullParams q, const dou
                                                          int32_t* __restrict__ idx, const int64_t* __restrict__ total,
                                                          int64_t cap) {
   __shared__ int32_t cand_all[kTB][kWordsPer * 64];
-  __shared__ double boxes[kTB][6];
+  __shared__ __align__(16) double boxes[kTB][6];
   __shared__ int32_t hits[kTB][kTB];  // [wave][tile]
   if (MODE && *total > cap) return;  // uniform across the grid
   const int s = blockIdx.x;
@@ -600,18 +611,13 @@ __global__ void __launch_bounds__(64 * kTB) k_tile_lists(CullParams q, const dou
     boxes[u][c] = (tx < q.lcols && ty < q.lrows) ? tile[8 * ((int64_t)ty * q.tiles_x + tx) + c] : (double)NAN;
   }
   __syncthreads();
-  int cnt[kTB];
-  int64_t pos[kTB];
-#pragma unroll
-  for (int u = 0; u < kTB; ++u) {
-    cnt[u] = 0;
-    pos[u] = 0;
-    if (MODE) {
-      const int tx = sx * kSB + u % kSB, ty = sy * kSB + u / kSB;
-      if (tx < q.lcols && ty < q.lrows) {
-        pos[u] = counts[(int64_t)ty * q.tiles_x + tx];
-        for (int w = 0; w < wv; ++w) pos[u] += part[((int64_t)s * kTB + w) * kTB + u];
-      }
+  int32_t cnt = 0;  // lane u: hits of this wave for tile u
+  int64_t pos = 0;  // lane u (MODE 1): where the next of them goes
+  if (MODE && lane < kTB) {
+    const int tx = sx * kSB + lane % kSB, ty = sy * kSB + lane / kSB;
+    if (tx < q.lcols && ty < q.lrows) {
+      pos = counts[(int64_t)ty * q.tiles_x + tx];
+      for (int w = 0; w < wv; ++w) pos += part[((int64_t)s * kTB + w) * kTB + lane];
     }
   }
   // superblocks wholly right of the launched columns or below the launched rows have no mask row
@@ -622,42 +628,43 @@ __global__ void __launch_bounds__(64 * kTB) k_tile_lists(CullParams q, const dou
     int32_t* const cand = cand_all[wv];
     for (int64_t w0 = wlo; w0 < whi; w0 += kWordsPer) {
       const uint64_t myword = (lane < kWordsPer && w0 + lane < whi) ? mrow[w0 + lane] : 0ull;
-      const int c = __popcll(myword);
-      int pre = c;  // inclusive prefix of the set-bit counts over the word lanes
-      for (int o = 1; o < kWordsPer; o <<= 1) {
-        const int v = __shfl_up(pre, o, 64);
-        if (lane >= o) pre += v;
+      int total_c = 0;  // uniform
+#pragma unroll 1
+      for (int k = 0; k < kWordsPer; ++k) {  // lane l takes bit l of word k
+        const uint64_t m = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(myword >> 32), k) << 32) |
+                           (uint32_t)__builtin_amdgcn_readlane((int)myword, k);
+        if (m == 0) continue;  // uniform
+        if ((m >> lane) & 1)
+          cand[total_c + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] =
+              (int32_t)((w0 + k) * 64 + lane);
+        total_c += __popcll(m);
       }
-      const int total = __shfl(pre, kWordsPer - 1, 64);
-      if (total == 0) continue;  // uniform
-      int at = pre - c;
-      uint64_t m = myword;
-      while (m) {
-        cand[at++] = (int32_t)((w0 + lane) * 64 + __builtin_ctzll(m));
-        m &= m - 1;
-      }
+      if (total_c == 0) continue;  // uniform
       wave_sync();
-      for (int k0 = 0; k0 < total; k0 += 64) {
-        const bool have = k0 + lane < total;
+      for (int k0 = 0; k0 < total_c; k0 += 64) {
+        const bool have = k0 + lane < total_c;
         int32_t r = 0;
-        double cr[13];
-        for (int k = 0; k < 13; ++k) cr[k] = 0.0;
+        double c[13];
+        for (int k = 0; k < 13; ++k) c[k] = 0.0;
         if (have) {
           r = cand[k0 + lane];
-          for (int k = 0; k < 13; ++k) cr[k] = cull[FDTBX_CULL_DOUBLES * (int64_t)r + k];
+          for (int k = 0; k < 13; ++k) c[k] = cull[FDTBX_CULL_DOUBLES * (int64_t)r + k];
         }
-#pragma unroll
+        const bool alive = c[12] != 0.0, wedge = c[8] >= 0.0;
+#pragma unroll 2
         for (int u = 0; u < kTB; ++u) {
-          const bool hit = have && cull_test(boxes[u], cr);
+          const bool hit = alive & cull_test_alive(boxes[u], c, wedge);
           const uint64_t hm = __ballot(hit);
+          if (hm == 0) continue;  // uniform
           if (MODE) {
-            if (hit) {
-              const uint64_t below = lane ? (hm & ((~0ull) >> (64 - lane))) : 0ull;
-              idx[pos[u] + __popcll(below)] = r;
-            }
-            pos[u] += __popcll(hm);
+            const int64_t at = ((int64_t)__builtin_amdgcn_readlane((int)(pos >> 32), u) << 32) |
+                               (uint32_t)__builtin_amdgcn_readlane((int)pos, u);
+            if (hit)
+              idx[at + __builtin_amdgcn_mbcnt_hi((unsigned)(hm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)hm, 0u))] = r;
+            if (lane == u) pos += __popcll(hm);
           } else {
-            cnt[u] += __popcll(hm);
+            if (lane == u) cnt += __popcll(hm);
           }
         }
       }
@@ -665,12 +672,9 @@ __global__ void __launch_bounds__(64 * kTB) k_tile_lists(CullParams q, const dou
     }
   }
   if (!MODE) {
-    if (lane == 0) {
-#pragma unroll
-      for (int u = 0; u < kTB; ++u) {
-        hits[wv][u] = cnt[u];
-        part[((int64_t)s * kTB + wv) * kTB + u] = cnt[u];
-      }
+    if (lane < kTB) {
+      hits[wv][lane] = cnt;
+      part[((int64_t)s * kTB + wv) * kTB + lane] = cnt;
     }
     __syncthreads();
     if (threadIdx.x < kTB) {
