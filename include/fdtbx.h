@@ -374,11 +374,12 @@ int fdtbx_profile(const fdtbx_model* model, const float* refl, const float* node
  *   pair_cap  capacity of idx: offsets[n_tiles] must not exceed it (units beyond the
  *             workspace's capacity, which only a larger total would need, are not run)
  *   ws        device workspace of fdtbx_profile_balanced_workspace(model, pair_cap) bytes:
- *             about 260 bytes per unit, for max(min(8192, pair_cap), min(2^19, ceil(pair_cap /
- *             16))) units plus one per tile when unit_pairs is 0 (at most 136 MB besides the
- *             tiles), ceil(pair_cap / unit_pairs) plus one per tile otherwise
+ *             about 260 bytes per unit, for max(min(8192, pair_cap), min(2^15, ceil(pair_cap /
+ *             16)), min(2^19, ceil(pair_cap / 32))) units plus one per tile when unit_pairs is 0
+ *             (at most 136 MB besides the tiles), ceil(pair_cap / unit_pairs) plus one per tile
+ *             otherwise
  * fdtbx_unit_pairs(n): the library's pairs per unit for n culled pairs, max(min(16,
- * ceil(n / 8192)), ceil(n / 2^19)) (32 for n = 0, 0 for n < 0). */
+ * ceil(n / 8192)), min(32, ceil(n / 2^15)), ceil(n / 2^19)) (32 for n = 0, 0 for n < 0). */
 int64_t fdtbx_unit_pairs(int64_t n_pairs);
 size_t fdtbx_profile_balanced_workspace(const fdtbx_model* model, int64_t pair_cap);
 int fdtbx_profile_balanced(const fdtbx_model* model, const float* refl, const float* nodes, const double* pix,

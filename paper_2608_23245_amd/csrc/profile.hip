@@ -146,14 +146,24 @@ __global__ void __launch_bounds__(256) k_unit_fill(ProfParams q, UnitTable T, co
   for (int64_t k = 0; k < n && s + k < T.max_units; ++k) T.unit_slot[s + k] = (int32_t)b;
 }
 
+// Whether the launch splits its walk (SPLIT of pairs_sum): the second queue pays where a pair's
+// queue is long, that is with dense node grids.  Forward launch split / not split at 32, 48, 56,
+// 64, 96, 128 nodes per side (medium workload cut at 3 A): Laue 9.33/9.05, 17.4/17.2, 22.6/22.6,
+// 28.7/28.7, 59.8/62.1, 104.2/108.2 ms; Gaussian 6.16/5.81, 10.41/10.46, 13.2/13.6, 16.4/17.3,
+// 34.2/37.3, 58.8/64.7 ms; 0.600/0.571 ms for a draft of 24 nodes per side.  The Hosemann
+// lineshape, whose support is one period, is never split (0.415/0.355 ms, the latter at 6 waves
+// per SIMD).
+constexpr int32_t kSplitNodes = 52;
+
 // Persistent: every wave takes units until none is left (for_units).
-template <int LS>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) k_profile_units(ProfParams q, const float* __restrict__ refl,
+template <int LS, bool SPLIT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LS == FDTBX_LINESHAPE_HOSEMANN ? 6 : 7))) k_profile_units(ProfParams q, const float* __restrict__ refl,
                                                        const float* __restrict__ nodes, const double* __restrict__ pix,
                                                        const double* __restrict__ tile, const int64_t* __restrict__ offsets,
                                                        const int32_t* __restrict__ idx, UnitTable T,
                                                        float* __restrict__ partials) {
-  __shared__ float4 qn[256 * 4];
+  constexpr int kQ = SPLIT ? 256 : 128;  // queue entries per wave
+  __shared__ float4 qn[kQ * 4];
   __shared__ int bq[64 * 4];
   __shared__ int qk[LS == FDTBX_LINESHAPE_HOSEMANN ? 128 * 4 : 1];  // node indices (support edge)
   const int wv = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
@@ -165,7 +175,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) k
     if (t < 0) return;
     const TilePixel px = tile_pixel(q, pix, tile, t, lane);
     unsigned long long cnt = 0;
-    partials[u * 64 + lane] = pairs_sum<false, LS>(q, refl, nodes, idx, px.box, px.R, px.Z, p0, p1, 64, qn + 256 * wv,
+    partials[u * 64 + lane] = pairs_sum<false, LS, false, SPLIT>(q, refl, nodes, idx, px.box, px.R, px.Z, p0, p1, 64, qn + kQ * wv,
                                                    bq + 64 * wv, cnt,
                                                    LS == FDTBX_LINESHAPE_HOSEMANN ? qk + 128 * wv : nullptr);
   });
@@ -381,17 +391,17 @@ int launch_batch_profile_stacked(const fdtbx_batch_entry* ent, const int64_t* so
 }
 
 // The persistent grid: as many 4-wave workgroups as the compute units hold at once.
-template <int LS>
+template <int LS, bool SPLIT>
 static int launch_units(const ProfParams& q, const float* refl, const float* nodes, const double* pix,
                         const double* tile, const int64_t* offsets, const int32_t* idx, const UnitTable& T,
                         float* partials, hipStream_t s) {
   int dev = 0, cus = 0, per_cu = 0;
   FDTBX_HIP(hipGetDevice(&dev));
   FDTBX_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-  FDTBX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(&k_profile_units<LS>),
+  FDTBX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(&k_profile_units<LS, SPLIT>),
                                                          256, 0));
   const unsigned n_wg = (unsigned)(cus > 0 ? cus : 1) * (unsigned)(per_cu > 0 ? per_cu : 1);
-  hipLaunchKernelGGL(k_profile_units<LS>, dim3(n_wg), dim3(256), 0, s, q, refl, nodes, pix, tile, offsets, idx, T,
+  hipLaunchKernelGGL((k_profile_units<LS, SPLIT>), dim3(n_wg), dim3(256), 0, s, q, refl, nodes, pix, tile, offsets, idx, T,
                      partials);
   FDTBX_LAUNCH_CHECK("balanced profile");
   return FDTBX_OK;
@@ -424,13 +434,15 @@ int launch_balanced(const fdtbx_model* model, const float* refl, const float* no
   FDTBX_LAUNCH_CHECK("balanced profile: unit scan");
   hipLaunchKernelGGL(k_unit_fill, dim3(gp), dim3(256), 0, s, q, T, offsets);
   FDTBX_LAUNCH_CHECK("balanced profile: unit fill");
+  auto launch = [&](auto units) { return units(q, refl, nodes, pix, tile, offsets, idx, T, partials, s); };
+  const bool split = q.n >= kSplitNodes;
   int rc;
   if (q.lineshape == FDTBX_LINESHAPE_GAUSSIAN)
-    rc = launch_units<FDTBX_LINESHAPE_GAUSSIAN>(q, refl, nodes, pix, tile, offsets, idx, T, partials, s);
+    rc = split ? launch(launch_units<FDTBX_LINESHAPE_GAUSSIAN, true>) : launch(launch_units<FDTBX_LINESHAPE_GAUSSIAN, false>);
   else if (q.lineshape == FDTBX_LINESHAPE_HOSEMANN)
-    rc = launch_units<FDTBX_LINESHAPE_HOSEMANN>(q, refl, nodes, pix, tile, offsets, idx, T, partials, s);
+    rc = launch(launch_units<FDTBX_LINESHAPE_HOSEMANN, false>);
   else
-    rc = launch_units<FDTBX_LINESHAPE_LAUE>(q, refl, nodes, pix, tile, offsets, idx, T, partials, s);
+    rc = split ? launch(launch_units<FDTBX_LINESHAPE_LAUE, true>) : launch(launch_units<FDTBX_LINESHAPE_LAUE, false>);
   if (rc) return rc;
   hipLaunchKernelGGL(k_unit_reduce, dim3((unsigned)L.n_slots), dim3(64), 0, s, q, T, pix, tile, offsets,
                      (const float*)partials, image);

@@ -74,24 +74,24 @@ __host__ __device__ inline int64_t ceil_div_dev(int64_t a, int64_t b) { return (
 // culled pairs, a function of the pair count alone, so that the image does not depend on the
 // device.  A unit's cost besides its pairs (its queue entry, pixel coordinates, a set-up that
 // fills only U of the 64 lanes, 256 bytes of sums) is about a third of a pair's, so 16 pairs lose
-// little, and a launch needs more units than the 7168 waves of a card to fill it: as many units
-// as 8192 where that takes fewer than 16 pairs each, and at most 2^19 units besides one partial
-// unit per tile.  Forward / adjoint at 1, 4, 16, 32, 64 pairs: 2,380 pairs 66/63/127/222/283 and
-// 56/76/199/366/473 us; 33,424 pairs 162/113/131/179/289 and 145/138/201/287/457 us; 490,639
-// pairs 1206/519/413/445/551 and 967/580/551/630/772 us; 28.9 million pairs 72.5/54.0/50.5/50.0/
-// 50.8 and 134/121/120/120/122 ms.
-constexpr int64_t kUnitTarget = int64_t{1} << 19, kUnitFew = 8192, kUnitPairs = 16;
+// little, and a launch needs more units than the 7168 waves of a card to fill it: 8192 units while
+// that takes at most 16 pairs each, 2^15 while that takes at most 32, and at most 2^19, besides one
+// partial unit per tile.  Forward / adjoint at 1, 4, 16, 32, 64 pairs: 2,380 pairs 66/63/127/222/283
+// and 56/76/199/366/473 us; 33,424 pairs 162/113/131/179/289 and 145/138/201/287/457 us; 490,639
+// pairs 1206/519/413/445/551 and 967/580/551/630/772 us; 759,346 pairs 1086/671/567/569/546 and
+// 1507/1036/1030/1073/1129 us; 28.9 million pairs 72.5/54.0/50.5/50.0/50.8 and 134/121/120/120/122
+// ms.
+constexpr int64_t kUnitTarget = int64_t{1} << 19, kUnitSome = int64_t{1} << 15, kUnitFew = 8192;
+__host__ __device__ inline int64_t min64(int64_t a, int64_t b) { return a < b ? a : b; }
+__host__ __device__ inline int64_t max64(int64_t a, int64_t b) { return a > b ? a : b; }
 __host__ __device__ inline int64_t default_unit_pairs(int64_t n_pairs) {
   if (n_pairs == 0) return 32;  // no unit at all: any size will do
-  const int64_t few = (n_pairs + kUnitFew - 1) / kUnitFew, most = (n_pairs + kUnitTarget - 1) / kUnitTarget;
-  const int64_t U = few < kUnitPairs ? few : kUnitPairs;
-  return U < most ? most : U;
+  return max64(max64(min64(16, ceil_div_dev(n_pairs, kUnitFew)), min64(32, ceil_div_dev(n_pairs, kUnitSome))),
+               ceil_div_dev(n_pairs, kUnitTarget));
 }
 // The most units (besides one per tile) that default_unit_pairs gives for at most cap pairs.
 inline int64_t most_units(int64_t cap) {
-  const int64_t few = cap < kUnitFew ? cap : kUnitFew, n = ceil_div(cap, kUnitPairs);
-  const int64_t many = n < kUnitTarget ? n : kUnitTarget;
-  return few > many ? few : many;
+  return max64(max64(min64(cap, kUnitFew), min64(ceil_div(cap, 16), kUnitSome)), min64(ceil_div(cap, 32), kUnitTarget));
 }
 
 // Mirror folds.  Tile column tiles_x - 1 - tx holds the left-right mirror pixels of column tx

@@ -116,3 +116,23 @@ def test_batch_adjoint_parts(side):
     want = B.profile_adjoint(model, eng.refl, eng.nodes, eng.pix, eng.tile, off, eng.idx, G.view(side, side))
     s = want.abs().amax(dim=0).clamp(min=1e-300)
     assert ((eng.sums - want).abs() / s).max().item() <= 1e-6
+
+
+@pytest.mark.parametrize("lineshape", [0, 1, 2])
+@pytest.mark.parametrize("n_nodes", [51, 52])
+def test_split_and_unsplit_walk(lineshape, n_nodes):
+    """The balanced launch on both sides of the node count from which its walk is split in two
+    queues, against the per-tile launch (whose walk always is): the same terms, two queues' block
+    sums against one's (2e-6 of the largest value)."""
+    wl = W.small(95, width=33, height=26, sigma_theta=0.05, gamma_theta=0.02, n_nodes=n_nodes, lineshape=lineshape)
+    model = B.make_model(wl)
+    hkl = B.enumerate_hkl(model.cell, wl.quad.d_min, wl.quad.d_max)
+    _, F2 = B.structure_factors(model.cell, atoms_to_device(wl.atoms), hkl, want_F=False)
+    refl, cull = B.reflection_prep(model, hkl, F2)
+    nodes = B.node_table(model)
+    pix, tile = B.pixel_map(model.geom)
+    off, idx = B.cull(model.geom, tile, cull)
+    print(f"split walk, lineshape {lineshape}, {n_nodes} nodes: {idx.numel()} pairs", flush=True)
+    img = B.profile_balanced(model, refl, nodes, pix, tile, off, idx)
+    ref = B.profile(model, refl, nodes, pix, tile, off, idx)
+    assert ref.max().item() > 0 and (img - ref).abs().max().item() <= 2e-6 * ref.max().item()
