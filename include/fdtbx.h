@@ -426,6 +426,16 @@ int fdtbx_profile_cyl(const fdtbx_model* model, const float* refl, const float* 
                       const int64_t* offsets, const int32_t* idx, const int32_t* order, double arc, float* image,
                       int64_t* counts, void* stream);
 
+/* fdtbx_profile_cyl with the tiles of a small detector shared among several workgroups each,
+ * whose sums are kept in ws and added in a fixed order: the same image up to the order of a
+ * tile's float32 sums, and the same bits on every run.
+ *   ws  device workspace of at least fdtbx_cyl_workspace(geom) bytes, which is 0 (ws may be
+ *       NULL) for a detector whose tiles fill the device as they are */
+size_t fdtbx_cyl_workspace(const fdtbx_geometry* geom);
+int fdtbx_profile_cyl_split(const fdtbx_model* model, const float* refl, const float* nodes, const double* pix,
+                            const int64_t* offsets, const int32_t* idx, const int32_t* order, double arc, float* image,
+                            void* ws, size_t ws_bytes, void* stream);
+
 /* Culling records (layout of fdtbx_reflection_prep's) for fdtbx_profile_cyl: with rho the
  * support corner radius sum_i w_i |a*_i| and rho_B = 2 r0 sqrt((1 - c_min)/2) + rho,
  * [0..3] = R_D -+ rho_B, D_z -+ rho_B, [4..5] = (max(r0 - rho, 0))^2, (r0 + rho)^2, wedge

@@ -118,6 +118,9 @@ _SIGS = {
     "fdtbx_tile_order": (ctypes.c_int, [ctypes.c_void_p] * 4 + [ctypes.c_size_t, ctypes.c_void_p]),
     "fdtbx_profile_cyl": (ctypes.c_int, [ctypes.c_void_p] * 7 + [ctypes.c_double, ctypes.c_void_p, ctypes.c_void_p,
                                                                    ctypes.c_void_p]),
+    "fdtbx_cyl_workspace": (ctypes.c_size_t, [ctypes.c_void_p]),
+    "fdtbx_profile_cyl_split": (ctypes.c_int, [ctypes.c_void_p] * 7 + [ctypes.c_double, ctypes.c_void_p, ctypes.c_void_p,
+                                                                       ctypes.c_size_t, ctypes.c_void_p]),
     "fdtbx_cyl_records": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p]),
     "fdtbx_profile_points": (ctypes.c_int, [ctypes.c_void_p] * 6 + [ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p]),
     "fdtbx_ewald_project": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p]),
@@ -491,8 +494,8 @@ def cyl_records(model: Model, hkl) -> torch.Tensor:
 
 
 def profile_cyl(model: Model, refl, nodes, pix, offsets, idx, arc: float, count=False, order=None):
-    """fdtbx_profile_cyl: the cylindrically averaged image [H][W] float32, or (count=True) the
-    number of support-passing evaluations.  order: fdtbx_tile_order of the lists, or None."""
+    """fdtbx_profile_cyl_split: the cylindrically averaged image [H][W] float32, or (count=True,
+    fdtbx_profile_cyl) the number of support-passing evaluations.  order: fdtbx_tile_order of the lists, or None."""
     g = model.geom
     if count:
         c = torch.zeros(1, dtype=torch.int64, device="cuda")
@@ -500,8 +503,10 @@ def profile_cyl(model: Model, refl, nodes, pix, offsets, idx, arc: float, count=
                                        _ptr(order), float(arc), None, _ptr(c), _stream()))
         return int(c.item())
     img = torch.empty((g.height, g.width), dtype=torch.float32, device="cuda")
-    _check(lib().fdtbx_profile_cyl(ctypes.byref(model), _ptr(refl), _ptr(nodes), _ptr(pix), _ptr(offsets), _ptr(idx),
-                                   _ptr(order), float(arc), _ptr(img), None, _stream()))
+    nbytes = lib().fdtbx_cyl_workspace(ctypes.byref(g))
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    _check(lib().fdtbx_profile_cyl_split(ctypes.byref(model), _ptr(refl), _ptr(nodes), _ptr(pix), _ptr(offsets), _ptr(idx),
+                                         _ptr(order), float(arc), _ptr(img), _ptr(ws), nbytes, _stream()))
     return img
 
 

@@ -8,7 +8,8 @@
 // Lorentz factor of Eq. lorentz), every point of the ring is visited; no Lorentz factor enters.
 //
 // Mapping: one to four 64-lane waves per pixel tile (8x8 by default) over the tile's list under the cylindrical
-// culling description (fdtbx_cyl_records).  Per (tile, reflection) each lane bounds the part
+// culling description (fdtbx_cyl_records); where a detector has few tiles, several such
+// workgroups per tile.  Per (tile, reflection) each lane bounds the part
 // of its ring that can reach the reflection's support (the ball of radius rho_B about D) and
 // the wave steps a shared index j over the union of those ranges, kJB indices at a time; the
 // 64 x kJB ring points of a step are treated like the splat's samples: node window from their
@@ -27,10 +28,28 @@ namespace fdtbx {
 struct CylParams {
   ProfParams q;
   double arc;
+  int32_t parts;  // workgroups per tile
 };
 
 // Ring indices evaluated together: they share the node window, queue and walk.
 constexpr int kJB = 8;
+
+// Workgroups per tile (cyl_parts): enough that a detector of few tiles, whose longest lists
+// alone decide the time when each tile is one workgroup, still gives every SIMD several waves
+// to choose from.  Measured with four waves per workgroup, ms with one / ceil(4096 / tiles) /
+// ceil(16384 / tiles) / ceil(65536 / tiles) workgroups per tile: 64x64 pixels (64 tiles)
+// 2.88 / 0.29 / 0.18 / 0.18, 224x224 (784) 1.44 / 0.37 / 0.33 / 0.36, 384x384 (2304)
+// 4.06 / 2.29 / 1.74 / 1.79; 1024x1024 (16384) is better with one: 140 against 156 with four.
+// At most kCylMaxParts: a list of 64x64 pixels has few pairs, and sharing the ring blocks of a
+// pair repeats its setup (0.29 ms with 32 parts, 0.18 with 128).
+constexpr int64_t kCylTarget = 16384;
+constexpr int64_t kCylMaxParts = 128;
+
+// Waves per SIMD that k_cyl is compiled for.  Its walk is a chain of transcendentals per
+// evaluation, and the two waves that its 163 to 210 registers allowed left the SIMDs idle
+// between them: 300 reflections over 1024x1024 pixels take 167 ms at two, 140 at three and
+// 135 at four, which spills 12 to 68 registers outside the walk.
+constexpr int kCylOccupancy = 4;
 
 // The queue walk of walk_queue, each entry evaluated at the lane's kJB ring points.
 template <bool COUNT, int LS>
@@ -97,15 +116,18 @@ __device__ __forceinline__ void walk_ring_edge(const ProfParams& q, const float4
   accr += fix;
 }
 
-// WAVES waves share a tile: per (tile, reflection), wave w takes the blocks w, w + WAVES, ...
-// of kJB ring indices (its own LDS queue), and wave 0 adds the others' pixel sums in wave
-// order at the end.
+// A tile's work is the pairs of its list times the blocks of kJB ring indices of each.
+// p.parts workgroups share it: with L pairs, part k takes the pairs k, k + G, ... for
+// G = min(parts, L), and where the list is shorter than the parts, parts / G workgroups share
+// the ring blocks of a pair as well.  Within a part, wave w of its WAVES takes every
+// (WAVES parts / G)-th block (its own LDS queue); wave 0 adds the others' pixel sums in wave
+// order, and k_cyl_sum the parts in part order, so the result does not depend on the launch.
 template <bool COUNT, int LS, int WAVES>
-__global__ void __launch_bounds__(64 * WAVES) k_cyl(CylParams p, const float* __restrict__ refl,
+__global__ void __launch_bounds__(64 * WAVES, kCylOccupancy) k_cyl(CylParams p, const float* __restrict__ refl,
                                                     const float* __restrict__ nodes, const double* __restrict__ pix,
                                                     const int64_t* __restrict__ offsets, const int32_t* __restrict__ idx,
                                                     float* __restrict__ image, unsigned long long* __restrict__ counts,
-                                                    const int32_t* __restrict__ order) {
+                                                    const int32_t* __restrict__ order, float* __restrict__ sums) {
   // the Hosemann support edge is decided in binary64 (walk_ring_edge): the queue then carries
   // its node indices in qk
   constexpr bool EDGE = LS == FDTBX_LINESHAPE_HOSEMANN && !COUNT;
@@ -119,7 +141,11 @@ __global__ void __launch_bounds__(64 * WAVES) k_cyl(CylParams p, const float* __
   float4* const qn = qn_all + 128 * wv;
   int* const bq = bq_all + 64 * wv;
   int* const qk = qk_all + (EDGE ? 128 * wv : 0);
-  const int t = order ? order[blockIdx.x] : tile_of_block(q, blockIdx.x);
+  // the parts of a tile are consecutive, so that the tiles with the longest lists, first in the
+  // order, also start first
+  const int part = p.parts > 1 ? (int)(blockIdx.x % (unsigned)p.parts) : 0;
+  const unsigned slot = p.parts > 1 ? blockIdx.x / (unsigned)p.parts : blockIdx.x;
+  const int t = order ? order[slot] : tile_of_block(q, slot);
   if (t < 0) return;  // uniform across the workgroup
   const int tx = t % q.tiles_x, ty = t / q.tiles_x;
   const int pi_ = (tx << q.tlg) + (lane & ((1 << q.tlg) - 1));
@@ -133,16 +159,21 @@ __global__ void __launch_bounds__(64 * WAVES) k_cyl(CylParams p, const float* __
   const double dphi = 2.0 * M_PI / (double)n;
   const int ring_lo = -(n / 2), ring_hi = n - n / 2 - 1;
   const double cd = cos(dphi), sd = sin(dphi);
-  // rotation over the blocks of the other waves
-  const double cw = WAVES > 1 ? cos((double)(kJB * (WAVES - 1)) * dphi) : 1.0;
-  const double sw = WAVES > 1 ? sin((double)(kJB * (WAVES - 1)) * dphi) : 0.0;
   const int64_t p0 = offsets[t], p1 = offsets[t + 1];
+  const int groups = p1 - p0 < p.parts ? (p1 > p0 ? (int)(p1 - p0) : 1) : p.parts;
+  const int ring_parts = p.parts / groups;
+  const int first = WAVES * (part / groups) + wv, stride = WAVES * ring_parts;  // in ring blocks
+  const bool idle = part / groups >= ring_parts;
+  // rotation over the blocks of the other waves
+  const double cw = cos((double)(kJB * (stride - 1)) * dphi);
+  const double sw = sin((double)(kJB * (stride - 1)) * dphi);
   float acc = 0.0f;
   unsigned long long cnt = 0;
-  int32_t r_next = p0 < p1 ? idx[p0] : 0;
-  for (int64_t pp = p0; pp < p1; ++pp) {
+  int64_t pp = p0 + (idle ? p1 - p0 : part % groups);
+  int32_t r_next = pp < p1 ? idx[pp] : 0;
+  for (; pp < p1; pp += groups) {
     const int32_t r = r_next;
-    r_next = idx[pp + 1 < p1 ? pp + 1 : pp];
+    r_next = idx[pp + groups < p1 ? pp + groups : pp];
     const float* rec = refl + (int64_t)FDTBX_REFL_FLOATS * r;
     PairRec f;
     load_pair(rec, f);
@@ -207,11 +238,11 @@ __global__ void __launch_bounds__(64 * WAVES) k_cyl(CylParams p, const float* __
       elo = q.half_m - band;
       ehi = q.half_m + band;
     }
-    double cj = cos((double)(J0 + kJB * wv) * dphi), sj = sin((double)(J0 + kJB * wv) * dphi);
+    double cj = cos((double)(J0 + kJB * first) * dphi), sj = sin((double)(J0 + kJB * first) * dphi);
     const float fZ = (float)(Z - ZD), fz = (float)Z;
     float accp = 0.0f;
     // kJB consecutive ring indices share one node window, queue and walk
-    for (int jb = J0 + kJB * wv; jb <= J1; jb += kJB * WAVES) {
+    for (int jb = J0 + kJB * first; jb <= J1; jb += kJB * stride) {
       float al[kJB][3];
       float amin[3] = {INFINITY, INFINITY, INFINITY}, amax[3] = {-INFINITY, -INFINITY, -INFINITY};
       float pmin[3] = {INFINITY, INFINITY, INFINITY}, pmax[3] = {-INFINITY, -INFINITY, -INFINITY};
@@ -238,7 +269,7 @@ __global__ void __launch_bounds__(64 * WAVES) k_cyl(CylParams p, const float* __
         sj = sj * cd + cj * sd;
         cj = cn;
       }
-      if (WAVES > 1) {
+      if (stride > 1) {
         const double cn = cj * cw - sj * sw;
         sj = sj * cw + cj * sw;
         cj = cn;
@@ -299,9 +330,36 @@ __global__ void __launch_bounds__(64 * WAVES) k_cyl(CylParams p, const float* __
       if (wv > 0) return;
       for (int k = 1; k < WAVES; ++k) acc += xacc[64 * (k - 1) + lane];
     }
-    if (!in) return;
-    write_folded(q, image, pi_, pj, tx, ty, acc * (float)(dphi / (2.0 * M_PI)));
+    acc *= (float)(dphi / (2.0 * M_PI));
+    if (p.parts > 1)
+      sums[64 * ((int64_t)part * q.lcols * q.lrows + (int64_t)ty * q.lcols + tx) + lane] = acc;
+    else if (in)
+      write_folded(q, image, pi_, pj, tx, ty, acc);
   }
+}
+
+// The parts' sums of each launched tile (one lane per pixel), added in part order.
+__global__ void __launch_bounds__(256) k_cyl_sum(ProfParams q, int parts, const float* __restrict__ sums,
+                                                 float* __restrict__ image) {
+  const int64_t n = 64 * (int64_t)q.lcols * q.lrows, i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const int tile = (int)(i >> 6), lane = (int)(i & 63);
+  const int tx = tile % q.lcols, ty = tile / q.lcols;
+  const int pi_ = (tx << q.tlg) + (lane & ((1 << q.tlg) - 1));
+  const int pj = ty * (64 >> q.tlg) + (lane >> q.tlg);
+  if (pi_ >= q.W || pj >= q.H) return;
+  float acc = 0.0f;
+#pragma unroll 8
+  for (int k = 0; k < parts; ++k) acc += sums[n * k + i];
+  write_folded(q, image, pi_, pj, tx, ty, acc);
+}
+
+// Workgroups per tile: a rule on the detector's tiles, folded or not, so that a folded image
+// has the sums of the unfolded one.
+static int cyl_parts(const fdtbx_geometry* g) {
+  const int64_t tiles = (int64_t)tiles_x_of(g) * tiles_y_of(g);
+  const int64_t want = ceil_div(kCylTarget, tiles);
+  return (int)(want < kCylMaxParts ? want : kCylMaxParts);
 }
 
 __global__ void k_zero_count(unsigned long long* c) {
@@ -311,56 +369,87 @@ __global__ void k_zero_count(unsigned long long* c) {
 template <int WAVES>
 static void launch_cyl(const CylParams& p, dim3 grid, hipStream_t s, const float* refl, const float* nodes,
                        const double* pix, const int64_t* offsets, const int32_t* idx, const int32_t* order, float* image,
-                       unsigned long long* counts) {
+                       unsigned long long* counts, float* sums) {
   const dim3 block(64 * WAVES);
   if (counts)
     hipLaunchKernelGGL((k_cyl<true, FDTBX_LINESHAPE_LAUE, WAVES>), grid, block, 0, s, p, refl, nodes, pix, offsets, idx, image,
-                       counts, order);
+                       counts, order, sums);
   else if (p.q.lineshape == FDTBX_LINESHAPE_GAUSSIAN)
     hipLaunchKernelGGL((k_cyl<false, FDTBX_LINESHAPE_GAUSSIAN, WAVES>), grid, block, 0, s, p, refl, nodes, pix, offsets, idx,
-                       image, counts, order);
+                       image, counts, order, sums);
   else if (p.q.lineshape == FDTBX_LINESHAPE_HOSEMANN)
     hipLaunchKernelGGL((k_cyl<false, FDTBX_LINESHAPE_HOSEMANN, WAVES>), grid, block, 0, s, p, refl, nodes, pix, offsets, idx,
-                       image, counts, order);
+                       image, counts, order, sums);
   else
     hipLaunchKernelGGL((k_cyl<false, FDTBX_LINESHAPE_LAUE, WAVES>), grid, block, 0, s, p, refl, nodes, pix, offsets, idx, image,
-                       counts, order);
+                       counts, order, sums);
 }
 
 }  // namespace fdtbx
 
 using namespace fdtbx;
 
-extern "C" int fdtbx_profile_cyl(const fdtbx_model* model, const float* refl, const float* nodes, const double* pix,
-                                 const int64_t* offsets, const int32_t* idx, const int32_t* order, double arc, float* image,
-                                 int64_t* counts, void* stream) {
-  if (!model || !refl || !nodes || !pix || !offsets || !idx) return fail(FDTBX_ERR_INVALID_ARGUMENT, "null pointer");
-  if (!counts && !image) return fail(FDTBX_ERR_INVALID_ARGUMENT, "image is NULL");
-  int rc = check_model(model);
-  if (rc) return rc;
+static int profile_cyl(const fdtbx_model* model, const float* refl, const float* nodes, const double* pix,
+                       const int64_t* offsets, const int32_t* idx, const int32_t* order, double arc, float* image,
+                       int64_t* counts, int parts, float* sums, void* stream) {
   if (!(arc >= 1.0e-5 && arc < 1.0)) return fail(FDTBX_ERR_INVALID_ARGUMENT, "arc must be in [1e-5, 1) 1/A");
   CylParams p;
   prof_params(model, &p.q);
   p.arc = arc;
+  p.parts = parts;
   // without an order: the plain tile order (the ring work of a few reflections concentrates on
   // a few superblocks, which the spatially grouped order would pile onto few XCDs)
   p.q.sbw = 0;
   hipStream_t s = (hipStream_t)stream;
-  const dim3 grid((unsigned)(order ? order_grid(p.q.lcols, p.q.lrows) : tile_grid(p.q)));
+  const int64_t tiles = (int64_t)p.q.lcols * p.q.lrows;
+  const dim3 grid((unsigned)(parts * (order ? order_grid(p.q.lcols, p.q.lrows) : tile_grid(p.q))));
   unsigned long long* cp = (unsigned long long*)counts;
   if (counts) {
     hipLaunchKernelGGL(k_zero_count, dim3(1), dim3(64), 0, s, cp);
     FDTBX_LAUNCH_CHECK("cylindrical average counter");
   }
   int waves = 1;
-  rc = tile_waves(&model->geom, (int64_t)p.q.lcols * p.q.lrows, &waves);
+  const int rc = tile_waves(&model->geom, tiles, &waves);
   if (rc) return rc;
   if (waves == 4)
-    launch_cyl<4>(p, grid, s, refl, nodes, pix, offsets, idx, order, image, cp);
+    launch_cyl<4>(p, grid, s, refl, nodes, pix, offsets, idx, order, image, cp, sums);
   else if (waves == 2)
-    launch_cyl<2>(p, grid, s, refl, nodes, pix, offsets, idx, order, image, cp);
+    launch_cyl<2>(p, grid, s, refl, nodes, pix, offsets, idx, order, image, cp, sums);
   else
-    launch_cyl<1>(p, grid, s, refl, nodes, pix, offsets, idx, order, image, cp);
+    launch_cyl<1>(p, grid, s, refl, nodes, pix, offsets, idx, order, image, cp, sums);
   FDTBX_LAUNCH_CHECK("cylindrical average");
+  if (!counts && parts > 1) {
+    hipLaunchKernelGGL(k_cyl_sum, dim3((unsigned)ceil_div(64 * tiles, 256)), dim3(256), 0, s, p.q, parts, sums, image);
+    FDTBX_LAUNCH_CHECK("cylindrical average sum");
+  }
   return FDTBX_OK;
+}
+
+extern "C" int fdtbx_profile_cyl(const fdtbx_model* model, const float* refl, const float* nodes, const double* pix,
+                                 const int64_t* offsets, const int32_t* idx, const int32_t* order, double arc, float* image,
+                                 int64_t* counts, void* stream) {
+  if (!model || !refl || !nodes || !pix || !offsets || !idx) return fail(FDTBX_ERR_INVALID_ARGUMENT, "null pointer");
+  if (!counts && !image) return fail(FDTBX_ERR_INVALID_ARGUMENT, "image is NULL");
+  const int rc = check_model(model);
+  if (rc) return rc;
+  return profile_cyl(model, refl, nodes, pix, offsets, idx, order, arc, image, counts, 1, nullptr, stream);
+}
+
+extern "C" size_t fdtbx_cyl_workspace(const fdtbx_geometry* geom) {
+  if (!geom || check_geometry(geom) != FDTBX_OK) return 0;
+  const int parts = cyl_parts(geom);
+  return parts > 1 ? (size_t)parts * lcols_of(geom) * lrows_of(geom) * 64 * sizeof(float) : 0;
+}
+
+extern "C" int fdtbx_profile_cyl_split(const fdtbx_model* model, const float* refl, const float* nodes, const double* pix,
+                                       const int64_t* offsets, const int32_t* idx, const int32_t* order, double arc,
+                                       float* image, void* ws, size_t ws_bytes, void* stream) {
+  if (!model || !refl || !nodes || !pix || !offsets || !idx || !image)
+    return fail(FDTBX_ERR_INVALID_ARGUMENT, "null pointer");
+  const int rc = check_model(model);
+  if (rc) return rc;
+  const size_t need = fdtbx_cyl_workspace(&model->geom);
+  if (ws_bytes < need || (need && !ws)) return fail(FDTBX_ERR_BUFFER_TOO_SMALL, "cylindrical average workspace too small");
+  return profile_cyl(model, refl, nodes, pix, offsets, idx, order, arc, image, nullptr, cyl_parts(&model->geom), (float*)ws,
+                     stream);
 }
