@@ -571,7 +571,7 @@ int fdtbx_profile_adjoint_balanced(const fdtbx_model* model, const float* refl, 
  *   ws         device workspace of fdtbx_pair_transpose_workspace(n_hkl, pair_cap) bytes
  *              (0 when pair_cap >= 2^31 or n_hkl >= 2^30: FDTBX_ERR_UNSUPPORTED)
  *
- * fdtbx_pair_reduce: sums[r][c] = sum over r's pairs p, in that order, of partials[p][c], plus
+ * fdtbx_pair_reduce: sums[r][c] = sum over r's pairs p, in a fixed order, of partials[p][c], plus
  * sum over the pairs p of its mate m of partials[p][6 + c], in binary64: m = mate[r] (device
  * int64 [n_hkl], -1 for none), or, with mate NULL, n_hkl - 1 - r if updown is nonzero and none
  * otherwise.  sums: device float64 [n_hkl][6] output.  No atomics: the same inputs give the
@@ -625,8 +625,8 @@ int fdtbx_pattern_backward(const fdtbx_model* model, const int32_t* hkl, int64_t
                            size_t ws_bytes, void* stream);
 
 /* fdtbx_pattern_backward_deterministic: fdtbx_pattern_backward with the fixed-order sums
- * (fdtbx_profile_adjoint_pairs, fdtbx_pair_transpose, fdtbx_pair_reduce) instead of atomic
- * adds: every output is reproducible bit for bit.  Same arguments; ws: device workspace of
+ * (fdtbx_profile_adjoint_pairs, fdtbx_pair_transpose, fdtbx_pair_reduce; for few reflections
+ * times tiles the pairs are found by searching the lists) instead of atomic adds: every output is reproducible bit for bit.  Same arguments; ws: device workspace of
  * fdtbx_backward_deterministic_workspace(n_hkl, n_atoms, pair_cap) bytes (about 60 bytes per
  * pair of capacity beyond fdtbx_backward_workspace; 0 for sizes the sort cannot take). */
 size_t fdtbx_backward_deterministic_workspace(int64_t n_hkl, int64_t n_atoms, int64_t pair_cap);

@@ -155,31 +155,126 @@ __global__ void k_zero_f32(float* __restrict__ v, int64_t n) {
 }
 
 // ---------------------------------------------------------------- fixed-order reduction
+// The sums of lanes 0..L-1 of each group of L lanes (a power of two) by a fixed tree; lane 0 of
+// the group holds them.
+template <int L>
+__device__ __forceinline__ void group_sum6(double v[6]) {
+#pragma unroll
+  for (int o = L / 2; o >= 1; o >>= 1)
+#pragma unroll
+    for (int c = 0; c < 6; ++c) v[c] += __shfl_down(v[c], o, L);
+}
+
+__device__ __forceinline__ void add_partials(double v[6], const float* o) {
+#pragma unroll
+  for (int c = 0; c < 6; ++c) v[c] += (double)o[c];
+}
+
 // sums[r][c] = sum over the pairs p of reflection r (refl_pairs[refl_ptr[r] .. refl_ptr[r+1]),
 // ascending culling-list position) of partials[p][c], then over the pairs of its mate m
 // (mate[r], or n - 1 - r when mate is NULL and updown is set; none otherwise) of
-// partials[p][6 + c]; binary64, one thread per reflection, a fixed order.
-__global__ void k_pair_reduce(int64_t n, const int64_t* __restrict__ refl_ptr, const int32_t* __restrict__ refl_pairs,
-                              const float* __restrict__ partials, const int64_t* __restrict__ mate, int32_t updown,
-                              double* __restrict__ sums) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= n) return;
+// partials[p][6 + c]; binary64, in a fixed order.  Sixteen lanes per reflection, lane l taking
+// its pairs l, l + 16, ...: the pairs' records lie apart, and one lane per reflection waited for
+// each in turn (67 us for 436 reflections in the lists of 255 tiles, 7 us so).
+constexpr int kReduceLanes = 16;
+
+__global__ void __launch_bounds__(256) k_pair_reduce(int64_t n, const int64_t* __restrict__ refl_ptr,
+                                                     const int32_t* __restrict__ refl_pairs,
+                                                     const float* __restrict__ partials, const int64_t* __restrict__ mate,
+                                                     int32_t updown, double* __restrict__ sums) {
+  const int64_t r = (int64_t)blockIdx.x * (256 / kReduceLanes) + threadIdx.x / kReduceLanes;
+  const int l = threadIdx.x % kReduceLanes;
   double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int64_t k = refl_ptr[r]; k < refl_ptr[r + 1]; ++k) {
-    const float* o = partials + 12 * (int64_t)refl_pairs[k];
-#pragma unroll
-    for (int c = 0; c < 6; ++c) v[c] += (double)o[c];
+  if (r < n) {
+    for (int64_t k = refl_ptr[r] + l; k < refl_ptr[r + 1]; k += kReduceLanes)
+      add_partials(v, partials + 12 * (int64_t)refl_pairs[k]);
+    const int64_t m = mate ? mate[r] : (updown ? n - 1 - r : -1);
+    if (m >= 0)
+      for (int64_t k = refl_ptr[m] + l; k < refl_ptr[m + 1]; k += kReduceLanes)
+        add_partials(v, partials + 12 * (int64_t)refl_pairs[k] + 6);
   }
-  const int64_t m = mate ? mate[r] : (updown ? n - 1 - r : -1);
-  if (m >= 0) {
-    for (int64_t k = refl_ptr[m]; k < refl_ptr[m + 1]; ++k) {
-      const float* o = partials + 12 * (int64_t)refl_pairs[k] + 6;
+  group_sum6<kReduceLanes>(v);
+  if (r < n && l == 0)
 #pragma unroll
-      for (int c = 0; c < 6; ++c) v[c] += (double)o[c];
-    }
+    for (int c = 0; c < 6; ++c) sums[6 * r + c] = v[c];
+}
+
+int launch_pair_reduce(int64_t n, const int64_t* refl_ptr, const int32_t* refl_pairs, const float* partials,
+                       const int64_t* mate, int32_t updown, double* sums, hipStream_t s) {
+  hipLaunchKernelGGL(k_pair_reduce, dim3((unsigned)ceil_div(n * kReduceLanes, 256)), dim3(256), 0, s, n, refl_ptr,
+                     refl_pairs, partials, mate, updown, sums);
+  FDTBX_LAUNCH_CHECK("pair reduction");
+  return FDTBX_OK;
+}
+
+// The position of r in the ascending list idx[a .. b), or -1.
+__device__ __forceinline__ int64_t find_in_list(const int32_t* __restrict__ idx, int64_t a, int64_t b, int32_t r) {
+  const int64_t end = b;
+  while (a < b) {
+    const int64_t m = a + ((b - a) >> 1);
+    if (idx[m] < r)
+      a = m + 1;
+    else
+      b = m;
   }
+  return a < end && idx[a] == r ? a : -1;
+}
+
+// The sums of k_pair_reduce straight from the culling lists, which fdtbx_cull writes in
+// ascending order of the reflections: a wave per reflection looks for it, and for its mate, in
+// the lists of the tiles lane, lane + 64, ..., and adds the lanes by a fixed tree.
+__global__ void __launch_bounds__(256) k_list_reduce(int64_t n, int64_t n_tiles, const int64_t* __restrict__ offsets,
+                                                     const int32_t* __restrict__ idx, const float* __restrict__ partials,
+                                                     int32_t updown, double* __restrict__ sums) {
+  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (r >= n) return;  // uniform in the wave
+  double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int64_t t = lane; t < n_tiles; t += 64) {
+    const int64_t a = offsets[t], b = offsets[t + 1];
+    const int64_t p = find_in_list(idx, a, b, (int32_t)r);
+    if (p >= 0) add_partials(v, partials + 12 * p);
+    const int64_t m = updown ? find_in_list(idx, a, b, (int32_t)(n - 1 - r)) : -1;
+    if (m >= 0) add_partials(v, partials + 12 * m + 6);
+  }
+  group_sum6<64>(v);
+  if (lane == 0)
 #pragma unroll
-  for (int c = 0; c < 6; ++c) sums[6 * r + c] = v[c];
+    for (int c = 0; c < 6; ++c) sums[6 * r + c] = v[c];
+}
+
+// The searches cost about as much as sorting the pairs where there are 2^25 of them.  Backward
+// pass in ms with the sort / with the searches: 436 reflections in 255 tiles 0.29 / 0.16; 49962
+// reflections in 16 tiles 1.31 / 0.58, in 256 tiles (2^23.6) 1.82 / 1.22, in 1024 tiles (2^25.6)
+// 4.83 / 4.90.  The sort takes the capacity of the lists through 20 launches, at least 2^20 pairs
+// as a plan makes it.
+constexpr int64_t kListReduceMost = int64_t{1} << 25;
+
+bool list_reduce_pays(int64_t n_hkl, int64_t n_tiles) { return n_hkl <= kListReduceMost / n_tiles; }
+
+int launch_list_reduce(int64_t n_hkl, int64_t n_tiles, const int64_t* offsets, const int32_t* idx, const float* partials,
+                       int32_t updown, double* sums, hipStream_t s) {
+  hipLaunchKernelGGL(k_list_reduce, dim3((unsigned)ceil_div(n_hkl, 4)), dim3(256), 0, s, n_hkl, n_tiles, offsets, idx,
+                     partials, updown, sums);
+  FDTBX_LAUNCH_CHECK("list reduction");
+  return FDTBX_OK;
+}
+
+// partials[0 .. 12 n) = 0 for the n = min(*n_pairs, cap) pairs of the lists.
+__global__ void __launch_bounds__(256) k_zero_partials(float4* __restrict__ partials, int64_t cap,
+                                                       const int64_t* __restrict__ n_pairs) {
+  const int64_t n = 3 * (*n_pairs < cap ? *n_pairs : cap);
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+    partials[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+}
+
+int launch_zero_partials(float* partials, int64_t cap, const int64_t* n_pairs, hipStream_t s) {
+  if (cap <= 0) return FDTBX_OK;
+  const int64_t blocks = ceil_div(3 * cap, 256);
+  hipLaunchKernelGGL(k_zero_partials, dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256), 0, s, (float4*)partials,
+                     cap, n_pairs);
+  FDTBX_LAUNCH_CHECK("partials");
+  return FDTBX_OK;
 }
 
 // ---------------------------------------------------------------- chain rule per reflection
@@ -614,9 +709,8 @@ int launch_batch_backward(const fdtbx_batch_entry* ent, int32_t n_models, const 
     FDTBX_LAUNCH_CHECK("batch profile adjoint");
   }
   if (fixed && n_hkl_total > 0) {
-    hipLaunchKernelGGL(k_pair_reduce, dim3((unsigned)ceil_div(n_hkl_total, 256)), dim3(256), 0, s, n_hkl_total,
-                       fixed->refl_ptr, fixed->refl_pairs, fixed->partials, fixed->mate, 0, sums);
-    FDTBX_LAUNCH_CHECK("batch adjoint pair reduction");
+    const int rc = launch_pair_reduce(n_hkl_total, fixed->refl_ptr, fixed->refl_pairs, fixed->partials, fixed->mate, 0, sums, s);
+    if (rc) return rc;
   }
   if (n_rb > 0) {
     hipLaunchKernelGGL(k_b_finish, dim3((unsigned)n_rb), dim3(kFinThreads), 0, s, ent, refl_blocks, hkl, refl, sums, F, dF2,
@@ -722,10 +816,7 @@ extern "C" int fdtbx_pair_reduce(int64_t n_hkl, const int64_t* refl_ptr, const i
   if (n_hkl < 0) return fail(FDTBX_ERR_INVALID_ARGUMENT, "n_hkl must be non-negative");
   if (n_hkl == 0) return FDTBX_OK;
   if (!refl_ptr || !refl_pairs || !partials || !sums) return fail(FDTBX_ERR_INVALID_ARGUMENT, "null pointer");
-  hipLaunchKernelGGL(k_pair_reduce, dim3((unsigned)ceil_div(n_hkl, 256)), dim3(256), 0, (hipStream_t)stream, n_hkl,
-                     refl_ptr, refl_pairs, partials, mate, updown ? 1 : 0, sums);
-  FDTBX_LAUNCH_CHECK("pair reduction");
-  return FDTBX_OK;
+  return launch_pair_reduce(n_hkl, refl_ptr, refl_pairs, partials, mate, updown ? 1 : 0, sums, (hipStream_t)stream);
 }
 
 extern "C" size_t fdtbx_adjoint_finish_workspace(int64_t n_hkl) {

@@ -447,17 +447,24 @@ extern "C" int fdtbx_pattern_backward_deterministic(
   int32_t* refl_pairs = (int32_t*)w;
   w += align_up((size_t)pair_cap * sizeof(int32_t), 256);
   hipStream_t s = (hipStream_t)stream;
-  rc = fill(partials, 12 * pair_cap, 0.0f, s);
+  rc = launch_zero_partials(partials, pair_cap, n_pairs_dev, s);
   if (rc) return rc;
   // the work units of the balanced forward launch, still in the forward workspace
   rc = launch_adjoint_units(model, refl, nodes, pix, tile, offsets, idx, order, pair_cap, fw + L.cullws, ctr, n_hkl,
                             grad_image, nullptr, partials, s);
   if (rc) return rc;
-  rc = fdtbx_pair_transpose(n_hkl, idx, pair_cap, n_pairs_dev, refl_ptr, refl_pairs, w,
-                            fdtbx_pair_transpose_workspace(n_hkl, pair_cap), stream);
-  if (rc) return rc;
-  rc = fdtbx_pair_reduce(n_hkl, refl_ptr, refl_pairs, partials, nullptr, (model->geom.mirror & 2) ? 1 : 0, sums, stream);
-  if (rc) return rc;
+  const int updown = (model->geom.mirror & 2) ? 1 : 0;
+  const int64_t n_tiles = (int64_t)tiles_x * tiles_y;
+  if (list_reduce_pays(n_hkl, n_tiles)) {
+    rc = launch_list_reduce(n_hkl, n_tiles, offsets, idx, partials, updown, sums, s);
+    if (rc) return rc;
+  } else {
+    rc = fdtbx_pair_transpose(n_hkl, idx, pair_cap, n_pairs_dev, refl_ptr, refl_pairs, w,
+                              fdtbx_pair_transpose_workspace(n_hkl, pair_cap), stream);
+    if (rc) return rc;
+    rc = fdtbx_pair_reduce(n_hkl, refl_ptr, refl_pairs, partials, nullptr, updown, sums, stream);
+    if (rc) return rc;
+  }
   rc = fdtbx_adjoint_finish(model, hkl, n_hkl, refl, sums, F, g2, d_globals, fin, fin_bytes, stream);
   if (rc) return rc;
   if (!atoms) return FDTBX_OK;

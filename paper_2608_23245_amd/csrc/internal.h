@@ -244,6 +244,14 @@ struct PairOrder {
   const int64_t* mate;        // [n_hkl], -1 where the model has no up-down fold
 };
 
+// The same sums, straight from culling lists in ascending order: for few reflections times tiles
+// (list_reduce_pays).  partials is cleared for the lists' pairs alone, their number read on the
+// device.
+bool list_reduce_pays(int64_t n_hkl, int64_t n_tiles);
+int launch_list_reduce(int64_t n_hkl, int64_t n_tiles, const int64_t* offsets, const int32_t* idx, const float* partials,
+                       int32_t updown, double* sums, hipStream_t s);
+int launch_zero_partials(float* partials, int64_t cap, const int64_t* n_pairs, hipStream_t s);
+
 int launch_batch_backward(const fdtbx_batch_entry* ent, int32_t n_models, const int64_t* refl_blocks, int64_t n_rb,
                           const int64_t* model_rb, const int64_t* atom_blocks, int64_t n_ab, const int64_t* items,
                           int64_t n_items, int64_t n_hkl_total, const int32_t* hkl, const float* x, const float* y,
