@@ -6,7 +6,7 @@
 // The phase h x + k y + l z is formed in binary64 (exact: integer times float32),
 // reduced modulo one turn there and only then rounded to float32, so the argument
 // of the hardware sine/cosine (which take revolutions) carries ~3e-8 turns of error
-// whatever the size of h.  Partial sums per atom chunk are reduced in a fixed order
+// whatever the size of h.  The sums of each atom chunk are reduced in a fixed order
 // in binary64: deterministic, no atomics.
 //
 // F(-h) = conj F(h): an enumerated list is symmetric, reflection n - 1 - i being the Friedel
@@ -16,8 +16,8 @@
 // Bound: the vector instructions of a term, 5 binary64 ones of 5 cycles per wave and SIMD, 3
 // transcendentals of 8.4 and 7 float32 ones of 2.6, or 68 cycles; 70 are reached.  The inner
 // loop reads the coordinates from LDS as binary64, converted once per atom and block, and
-// reduces the phase by v_fract_f64 alone (with a floor and a subtraction: 3.6 ms for 3.4).
-// 293298 reflections of 50000 atoms took 6.4 ms when every reflection was evaluated.
+// reduces the phase by v_fract_f64 alone (with a floor and a subtraction 7 % more).
+// 293298 reflections of 50000 atoms take 3.2 ms, 6.4 when every reflection was evaluated.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -28,7 +28,10 @@ namespace fdtbx {
 
 static constexpr int kSFThreads = 256;
 static constexpr int kMaxTypes = 16;
-static constexpr int kAtomsPerChunkMax = 2048;
+// Atoms summed in float32 before they are added in binary64.  The float32 sums of a whole chunk
+// were most of the error: 1.7e-7 to 6.4e-7 of |F| for 160 to 30000 atoms, 1.1e-7 so.
+static constexpr int kSFGroup = 8;
+static_assert(kSFThreads % kSFGroup == 0, "a partly filled group of atoms ends inside the LDS array");
 static constexpr int64_t kSFBlocks = 2048;  // two rounds of the chip's 256 compute units at four blocks each
 
 struct SFParams {
@@ -53,6 +56,11 @@ struct AtomsLds {
     xy[i] = make_double2((double)x[j], (double)y[j]);
     zb[i] = {(double)z[j], -B[j] * 1.4426950408889634f, o[j]};
     type[i] = t * row;
+  }
+  __device__ __forceinline__ void put_none(int i) {  // adds nothing
+    xy[i] = make_double2(0.0, 0.0);
+    zb[i] = {0.0, 0.0f, 0.0f};
+    type[i] = 0;
   }
 };
 
@@ -91,7 +99,8 @@ __global__ void __launch_bounds__(kSFThreads) k_sf_partial(SFParams p, const flo
   const int64_t a1 = a0 + p.chunk < p.n_atoms ? a0 + p.chunk : p.n_atoms;
   for (int second = 0; second < (mates ? 1 : 2); ++second) {  // uniform
     double h[K], kk[K], l[K];
-    float s2[K], re[K], im[K];
+    float s2[K];
+    double re[K], im[K];
     bool any = false;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
@@ -105,25 +114,37 @@ __global__ void __launch_bounds__(kSFThreads) k_sf_partial(SFParams p, const flo
       for (int j = 0; j < 3; ++j) D[j] = (h[k] * p.as[j] + kk[k] * p.as[3 + j]) + l[k] * p.as[6 + j];
       const double s2d = 0.25 * ((D[0] * D[0] + D[1] * D[1]) + D[2] * D[2]);
       s2[k] = (float)s2d;
-      re[k] = im[k] = 0.0f;
+      re[k] = im[k] = 0.0;
       for (int t = 0; t < p.n_types; ++t) ftab[(t * kSFThreads + threadIdx.x) * K + k] = form_factor(ff + 9 * t, s2d);
     }
     for (int64_t g0 = a0; g0 < a1; g0 += kSFThreads) {
       __syncthreads();
-      if (g0 + threadIdx.x < a1) at.put(threadIdx.x, x, y, z, B, occ, type, g0 + threadIdx.x, p.n_types, kSFThreads * K);
+      if (g0 + threadIdx.x < a1)
+        at.put(threadIdx.x, x, y, z, B, occ, type, g0 + threadIdx.x, p.n_types, kSFThreads * K);
+      else
+        at.put_none(threadIdx.x);
       __syncthreads();
       const int cnt = (int)((a1 - g0) < kSFThreads ? (a1 - g0) : kSFThreads);
       if (any) {
-        for (int i = 0; i < cnt; ++i) {
-          const double2 xy = at.xy[i];
-          const auto zb = at.zb[i];
-          const float* f = ftab + at.type[i] + threadIdx.x * K;
+        for (int i0 = 0; i0 < cnt; i0 += kSFGroup) {
+          float gr[K] = {}, gi[K] = {};
+#pragma unroll 4
+          for (int i = i0; i < i0 + kSFGroup; ++i) {
+            const double2 xy = at.xy[i];
+            const auto zb = at.zb[i];
+            const float* f = ftab + at.type[i] + threadIdx.x * K;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+              const float fr = sf_phase(h[k], kk[k], l[k], xy, zb.z);
+              const float amp = zb.occ * f[k] * __builtin_amdgcn_exp2f(zb.nBl2e * s2[k]);
+              gr[k] = fmaf(amp, __builtin_amdgcn_cosf(fr), gr[k]);
+              gi[k] = fmaf(amp, __builtin_amdgcn_sinf(fr), gi[k]);
+            }
+          }
 #pragma unroll
           for (int k = 0; k < K; ++k) {
-            const float fr = sf_phase(h[k], kk[k], l[k], xy, zb.z);
-            const float amp = zb.occ * f[k] * __builtin_amdgcn_exp2f(zb.nBl2e * s2[k]);
-            re[k] = fmaf(amp, __builtin_amdgcn_cosf(fr), re[k]);
-            im[k] = fmaf(amp, __builtin_amdgcn_sinf(fr), im[k]);
+            re[k] += (double)gr[k];
+            im[k] += (double)gi[k];
           }
         }
       }
@@ -132,8 +153,9 @@ __global__ void __launch_bounds__(kSFThreads) k_sf_partial(SFParams p, const flo
     for (int k = 0; k < K; ++k) {
       const int64_t i = i0 + k * kSFThreads, j = p.n_hkl - 1 - i;
       if (i >= half) continue;
-      if (!second) part[i] = make_float2(re[k], im[k]);
-      if (j != i && (second || mates)) part[j] = make_float2(re[k], second ? im[k] : -im[k]);
+      const float r32 = (float)re[k], i32 = (float)im[k];
+      if (!second) part[i] = make_float2(r32, i32);
+      if (j != i && (second || mates)) part[j] = make_float2(r32, second ? i32 : -i32);
     }
   }
 }
@@ -233,9 +255,7 @@ static int sf_split(int64_t n_hkl, int64_t n_atoms, int32_t* n_chunks, int64_t* 
   const int64_t half = (n_hkl + 1) / 2, maxc = ceil_div(n_atoms, 64);
   const int k = ceil_div(half, 2 * kSFThreads) * ceil_div(n_atoms, 1024) >= kSFBlocks ? 2 : 1;
   const int64_t nb = ceil_div(half, k * kSFThreads);
-  int64_t want = ceil_div(kSFBlocks, nb);                  // fill the chip
-  int64_t need = ceil_div(n_atoms, kAtomsPerChunkMax);     // and keep float32 partial sums short
-  int64_t nc = want > need ? want : need;
+  int64_t nc = ceil_div(kSFBlocks, nb);  // fill the chip
   if (nc > maxc) nc = maxc;
   if (nc < 1) nc = 1;
   *chunk = ceil_div(n_atoms, nc);

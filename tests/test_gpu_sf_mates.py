@@ -1,9 +1,9 @@
 """Structure factors of lists that are symmetric, in part or not at all, at the sizes where the
 kernel's split changes: one reflection, the middle of an odd list, one block's reflections (256
-or 512 of the first half) and the atoms of a chunk (64 and 2048).  Against the sum in binary64;
+or 512 of the first half) and the atoms of a chunk (64) and of a group (8).  Against the sum in binary64;
 a term carries the float32 rounding of its phase (1.9e-7 of its size), of its exponent and
-amplitude (under 2e-6 for exponents up to 10), and a chunk's float32 sum of up to 2048 terms adds
-a random walk of 6e-8 a step: 5e-6 of the sum of the amplitudes in all.  The mate of every
+amplitude (under 2e-6 for exponents up to 10), and a group's float32 sum of eight terms adds
+6e-8 a step: 5e-6 of the sum of the amplitudes in all.  The mate of every
 reflection in a symmetric list is its conjugate."""
 import math
 
