@@ -78,8 +78,7 @@ typedef struct fdtbx_geometry {
                                  of 8 ring indices of each pair; the forward's first wave adds the
                                  others' pixel sums in wave order); 0: the library's choice, 4 when the
                                  launched tiles fit in eight rounds of one-wave workgroups (32 per
-                                 compute unit), else 2.  The batched persistent kernels run one
-                                 wave per (model, tile) item whatever the value */
+                                 compute unit), else 2.  The batched kernels ignore it */
   int32_t unit_pairs;         /* pairs per work unit of fdtbx_profile_balanced (and so of
                                  fdtbx_profile_pattern): 0 is the library's choice from the pair
                                  count (fdtbx_unit_pairs); the image depends on it in the last bits
@@ -364,17 +363,19 @@ int fdtbx_profile(const fdtbx_model* model, const float* refl, const float* node
 
 /* fdtbx_profile_balanced: the image of fdtbx_profile (the same sum, Eqs. direct_sum and
  * lorentz) from a launch balanced over the compute units.  The launched tiles' lists are cut
- * into work units of geom.unit_pairs pairs (0: fdtbx_unit_pairs(n_pairs), read on the device
- * from offsets[n_tiles]); persistent waves take the units from eight queues, one per XCD
- * (slot b of the launch order feeds queue b % 8, in slot order), each unit writes its 64 pixel
- * sums to a slot of its own, and a second kernel adds each tile's units in unit order.  So no
+ * into work units of geom.unit_pairs pairs; 0: of fdtbx_unit_pairs(n_pairs) pairs (read on the
+ * device from offsets[n_tiles]), or from 8193 to 2048 n_nodes^2 pairs, of as many pairs of mean
+ * weight, a pair's weight being an estimate of its time from its node window.  Persistent waves take the
+ * units from queues, eight for each XCD (slot b of the launch order feeds those of XCD b % 8, in
+ * slot order), each unit writes its 64 pixel sums to a slot of its own, and a second kernel adds
+ * each tile's units in unit order.  So no
  * long list runs as one workgroup at the end of the launch, and the image is the same on every
  * run; it equals fdtbx_profile's to float32 rounding (the sums are grouped by unit).
  *   order     as for fdtbx_profile (or NULL)
  *   pair_cap  capacity of idx: offsets[n_tiles] must not exceed it (units beyond the
  *             workspace's capacity, which only a larger total would need, are not run)
  *   ws        device workspace of fdtbx_profile_balanced_workspace(model, pair_cap) bytes:
- *             about 260 bytes per unit, for max(min(8192, pair_cap), min(2^15, ceil(pair_cap /
+ *             about 264 bytes per unit, for max(min(8192, pair_cap), min(2^15, ceil(pair_cap /
  *             16)), min(2^19, ceil(pair_cap / 32))) units plus one per tile when unit_pairs is 0
  *             (at most 136 MB besides the tiles), ceil(pair_cap / unit_pairs) plus one per tile
  *             otherwise
@@ -543,7 +544,7 @@ int fdtbx_profile_adjoint(const fdtbx_model* model, const float* refl, const flo
                           int64_t n_hkl, const float* grad_image, double* sums, void* stream);
 
 /* fdtbx_profile_adjoint_balanced: fdtbx_profile_adjoint over the work units of a
- * fdtbx_profile_balanced call (persistent waves taking the units from the eight XCD queues, so
+ * fdtbx_profile_balanced call (persistent waves taking the units from the XCDs' queues, so
  * no long list runs as one workgroup at the end).  bal_ws, bal_ws_bytes: the workspace of that
  * call, with the same model (unit_pairs included), lists, order and pair_cap, and no other
  * balanced launch on it since; its unit tables are read and its queue counters reused.  The

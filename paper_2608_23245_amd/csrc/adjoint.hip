@@ -87,11 +87,10 @@ __global__ void __launch_bounds__(256) k_profile_adj_units(ProfParams q, const f
   __shared__ int bq[64 * 4];
   __shared__ int qk[LS == FDTBX_LINESHAPE_HOSEMANN ? 128 * 4 : 1];  // node indices (support edge)
   const int wv = (int)(threadIdx.x >> 6);
-  const int64_t U = T.meta[1];
-  const int64_t total = U > 0 ? min(T.meta[0], T.max_units) : 0;
+  const int64_t total = min(T.meta[0], T.max_units);
   for_units(T, total, [&](int64_t u) {
     int64_t p0, p1;
-    const int t = unit_range(q, T, offsets, u, U, &p0, &p1);
+    const int t = unit_range(q, T, offsets, u, total, &p0, &p1);
     if (t < 0) return;
     adjoint_range<LS>(q, refl, nodes, pix, tile, idx, grad_image, n_hkl, sums, partials, t, p0, p1, 64, 64, qn + 128 * wv,
                       qd + 128 * wv, bq + 64 * wv, gw + 128 * wv,

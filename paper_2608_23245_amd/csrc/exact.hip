@@ -47,27 +47,6 @@ __device__ static inline bool enum_keep(const EnumParams& p, int64_t idx, int32_
   return true;
 }
 
-// Exclusive scan over the block; *total gets the block sum.  blockDim.x is a multiple of 64.
-__device__ static int64_t block_exclusive_scan(int64_t v, int64_t* lds, int64_t* total) {
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  int64_t x = v;
-  for (int o = 1; o < 64; o <<= 1) {
-    int64_t y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
-  if (lane == 63) lds[wid] = x;
-  __syncthreads();
-  int64_t off = 0, tot = 0;
-  for (int w = 0; w < nw; ++w) {
-    int64_t s = lds[w];
-    if (w < wid) off += s;
-    tot += s;
-  }
-  __syncthreads();
-  *total = tot;
-  return off + x - v;
-}
-
 __global__ void __launch_bounds__(kEnumThreads) k_enum_count(EnumParams p, int64_t* block_counts) {
   __shared__ int64_t lds[kEnumThreads / 64];
   int64_t base = (int64_t)blockIdx.x * kEnumChunk + (int64_t)threadIdx.x * kEnumPerThread;

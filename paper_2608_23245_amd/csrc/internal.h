@@ -197,6 +197,27 @@ __host__ __device__ inline double lineshape_half(int32_t lineshape, int32_t m) {
   return lineshape == FDTBX_LINESHAPE_HOSEMANN ? 0.5 : 0.5 * (double)m;
 }
 
+// Exclusive scan over the block; *total gets the block sum.  blockDim.x is a multiple of 64.
+__device__ inline int64_t block_exclusive_scan(int64_t v, int64_t* lds, int64_t* total) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  int64_t x = v;
+  for (int o = 1; o < 64; o <<= 1) {
+    int64_t y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) lds[wid] = x;
+  __syncthreads();
+  int64_t off = 0, tot = 0;
+  for (int w = 0; w < nw; ++w) {
+    int64_t s = lds[w];
+    if (w < wid) off += s;
+    tot += s;
+  }
+  __syncthreads();
+  *total = tot;
+  return off + x - v;
+}
+
 // Exclusive scan of n values in place with one block of 1024 threads; writes the grand total
 // to *total (exact.hip).
 __global__ void k_scan_inplace(int64_t* v, int64_t n, int64_t* total);

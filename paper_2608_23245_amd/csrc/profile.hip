@@ -113,37 +113,158 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) k_
 // ---------------------------------------------------------------- balanced launch
 // The per-tile launch ends with a tail: a tile with a long list runs as one workgroup while
 // the compute units around it have drained.  The balanced launch cuts every launched tile's
-// list into units of at most U pairs, which persistent waves take from eight queues, one per
-// XCD: slot b of the per-tile launch order (the tile order of fdtbx_tile_order, whose slot b
-// runs on XCD b % 8) puts its tile's units in queue b % 8, in slot order (heavy tiles first
-// under the work order), so the units of neighbouring tiles still share an XCD's L2.  A wave
-// whose queue is empty takes units from the next queues.  Each unit writes its 64 pixel sums
+// list into units, which persistent waves take from queues, eight for each XCD: slot b of the
+// per-tile launch order (the tile order of fdtbx_tile_order, whose slot b runs on XCD b % 8) puts
+// its tile's units in the queues of XCD b % 8, in slot order (long lists first under the work
+// order), so the units of neighbouring tiles still share an XCD's L2.  A wave whose queue is
+// empty takes units from the others (for_units).  Each unit writes its 64 pixel sums
 // to its own slot of the partial sums, and a second kernel adds a tile's units in unit order:
 // the image does not depend on which wave ran which unit.
 //
-// Units per position (and the pairs per unit, from the pair count, by the first thread).
-__global__ void __launch_bounds__(256) k_unit_count(ProfParams q, UnitTable T, const int64_t* __restrict__ offsets,
-                                                    int64_t n_tiles) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t U = T.fixed_U > 0 ? T.fixed_U : default_unit_pairs(offsets[n_tiles]);
-  if (p == 0) T.meta[1] = U;
-  if (p < kQueues) T.ctr[p * kQueueStride] = 0;
-  if (p >= kXcds * T.nj) return;
-  const int64_t b = (p % T.nj) * kXcds + p / T.nj;
-  const int t = slot_tile(q, T, b);
-  T.qscan[p] = t >= 0 ? ceil_div_dev(offsets[t + 1] - offsets[t], U) : 0;
+// A pair's share of the time: its set-up, and the nodes of its window, which are scanned and in
+// part walked.  (Weights that grow faster with the window, n^1.5 and n^2, measured the same.)
+constexpr int kWeightPair = 16;
+__device__ inline int pair_weight(const ProfParams& q, const float* __restrict__ rec, const float* __restrict__ nodes,
+                                  const TileBox& box) {
+  int w01, w23;
+  float lo[3], hi[3];
+  if (!pair_setup<false>(q, rec, nodes, box, &w01, &w23, lo, hi)) return 2;
+  const int n = ((w01 >> 16) - (w01 & 0xffff) + 1) * ((w23 >> 16) - (w23 & 0xffff) + 1);
+  return kWeightPair + n;
 }
 
-// unit_slot over each slot's units (within the capacity).
-__global__ void __launch_bounds__(256) k_unit_fill(ProfParams q, UnitTable T, const int64_t* __restrict__ offsets) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Whether the lists of n_pairs pairs are cut by weight.  Pairs of one pattern differ a
+// hundredfold: a low-order reflection has every node in reach of a tile, most have a few.  Cut
+// by their number alone, single units of heavy pairs ran on for 40 % of a launch of 490,639
+// Hosemann pairs after the median wave had finished.  Weighing reads every pair's record twice,
+// about 40 us per million pairs, and what it saves grows with the nodes of a heavy pair.  Forward
+// + adjoint, cut by number / by weight, at 16 nodes per side: 28,657 pairs 0.120 + 0.148 / 0.109 +
+// 0.117 ms, 485,808 pairs 0.378 + 0.632 / 0.391 + 0.539, 1.8 million 0.754 + 1.356 / 0.848 +
+// 1.204, 7.2 million 2.36 + 4.37 / 2.65 + 4.22; at 64 nodes: 28,657 pairs 1.10 + 1.92 / 0.83 +
+// 1.42, 485,808 pairs 3.60 + 7.63 / 2.92 + 6.17, 7.2 million 22.4 + 49.1 / 21.7 + 46.4.
+static int64_t weigh_most(const ProfParams& q, int64_t fixed_U) {
+  return fixed_U > 0 ? -1 : (int64_t)q.n * q.n * 2048;  // 2^19 pairs at 16 nodes per side, 2^23 at 64
+}
+// Up to 8192 pairs a unit is one pair whatever its weight.
+__device__ inline bool weighed(const UnitTable& T, int64_t n_pairs) { return n_pairs > kUnitFew && n_pairs <= T.weigh_most; }
+
+__device__ inline int64_t pairs_per_unit(const UnitTable& T, int64_t n_pairs) {
+  return T.fixed_U > 0 ? T.fixed_U : default_unit_pairs(n_pairs);
+}
+
+__device__ inline TileBox tile_box(const double* __restrict__ tile, int t) {
+  return {tile[8 * (int64_t)t + 0], tile[8 * (int64_t)t + 1], tile[8 * (int64_t)t + 2], tile[8 * (int64_t)t + 3]};
+}
+
+// The weight of each position's list, one wave each: its pairs, or where the lists are weighed
+// the sum of their weights.  Also clears the queue counters.
+__global__ void __launch_bounds__(256) k_unit_weight(ProfParams q, UnitTable T, const int64_t* __restrict__ offsets,
+                                                     int64_t n_tiles, const float* __restrict__ refl,
+                                                     const float* __restrict__ nodes, const double* __restrict__ tile,
+                                                     const int32_t* __restrict__ idx) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < kQueues) T.ctr[i * kQueueStride] = 0;
+  const int64_t p = i >> 6;
+  const int lane = threadIdx.x & 63;
+  if (p >= kXcds * T.nj) return;
+  const int t = slot_tile(q, T, (p % T.nj) * kXcds + p / T.nj);
+  int64_t w = 0;
+  if (t >= 0) {
+    const int64_t o = offsets[t], e = offsets[t + 1];
+    if (weighed(T, offsets[n_tiles])) {
+      const TileBox box = tile_box(tile, t);
+      for (int64_t k = o + lane; k < e; k += 64) w += pair_weight(q, refl + (int64_t)FDTBX_REFL_FLOATS * idx[k], nodes, box);
+      for (int s = 32; s >= 1; s >>= 1) w += __shfl_xor(w, s, 64);
+    } else {
+      w = e - o;
+    }
+  }
+  if (lane == 0) T.weight[p] = w;
+}
+
+// One block: the weight W of a unit, that of as many mean pairs as a unit has, and the first
+// unit of each position, which has ceil(weight / W) of them.
+__global__ void __launch_bounds__(1024) k_unit_scan(UnitTable T, const int64_t* __restrict__ offsets, int64_t n_tiles) {
+  __shared__ int64_t lds[16];
+  const int64_t n = kXcds * T.nj, n_pairs = offsets[n_tiles], U = pairs_per_unit(T, n_pairs);
+  int64_t W = U;
+  if (weighed(T, n_pairs)) {
+    int64_t sum = 0, total;
+    for (int64_t i = threadIdx.x; i < n; i += 1024) sum += T.weight[i];
+    block_exclusive_scan(sum, lds, &total);
+    W = max64(1, ceil_div_dev(total, max64(1, n_pairs / U)));
+  }
+  constexpr int kPer = 8;
+  int64_t carry = 0;  // the same in every thread
+  for (int64_t b = 0; b < n; b += 1024 * kPer) {
+    const int64_t i = b + (int64_t)threadIdx.x * kPer;
+    int64_t x[kPer], sum = 0, tot;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      x[k] = i + k < n ? ceil_div_dev(T.weight[i + k], W) : 0;
+      sum += x[k];
+    }
+    int64_t at = carry + block_exclusive_scan(sum, lds, &tot);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      if (i + k < n) T.qscan[i + k] = at;
+      at += x[k];
+    }
+    carry += tot;
+  }
+  if (threadIdx.x == 0) {
+    T.meta[0] = carry;
+    T.meta[1] = U;
+  }
+}
+
+// The number of units of position p.
+__device__ inline int64_t units_at(const UnitTable& T, int64_t p) {
+  return (p + 1 < kXcds * T.nj ? T.qscan[p + 1] : T.meta[0]) - T.qscan[p];
+}
+
+// Each position's units (within the capacity), one wave per position: U pairs each, or where the
+// lists are weighed, with n units of a list of weight w, unit k from the first pair with
+// n (weight of the pairs before it) >= k w.  The cut depends on the list alone, not on its place
+// in the launch.
+__global__ void __launch_bounds__(256) k_unit_fill(ProfParams q, UnitTable T, const int64_t* __restrict__ offsets,
+                                                   int64_t n_tiles, const float* __restrict__ refl,
+                                                   const float* __restrict__ nodes, const double* __restrict__ tile,
+                                                   const int32_t* __restrict__ idx) {
+  const int64_t p = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
+  const int lane = threadIdx.x & 63;
   if (p >= kXcds * T.nj) return;
   const int64_t b = (p % T.nj) * kXcds + p / T.nj;
   const int t = slot_tile(q, T, b);
   if (t < 0) return;
-  const int64_t U = T.meta[1];
-  const int64_t n = ceil_div_dev(offsets[t + 1] - offsets[t], U), s = T.qscan[p];
-  for (int64_t k = 0; k < n && s + k < T.max_units; ++k) T.unit_slot[s + k] = (int32_t)b;
+  const int64_t s = T.qscan[p], U = T.meta[1], n = min64(units_at(T, p), T.max_units - s);
+  const bool by_weight = weighed(T, offsets[n_tiles]);
+  for (int64_t k = lane; k < n; k += 64) {
+    T.unit_slot[s + k] = (int32_t)b;
+    if (!by_weight || k == 0) T.unit_start[s + k] = (int32_t)(k * U);
+  }
+  if (!by_weight || n <= 1) return;
+  const TileBox box = tile_box(tile, t);
+  const double per = (double)units_at(T, p) / (double)T.weight[p];
+  const int64_t o = offsets[t], len = offsets[t + 1] - o;
+  int64_t before = 0;  // weight of the chunks before
+  int last = 0;        // unit of the pair before
+  for (int64_t k0 = 0; k0 < len; k0 += 64) {
+    const int64_t k = k0 + lane;
+    const int64_t w = k < len ? pair_weight(q, refl + (int64_t)FDTBX_REFL_FLOATS * idx[o + k], nodes, box) : 0;
+    int64_t c = w;
+    for (int d = 1; d < 64; d <<= 1) {
+      const int64_t y = __shfl_up(c, d, 64);
+      if (lane >= d) c += y;
+    }
+    const int unit = k < len ? (int)min((double)(n - 1), floor((double)(before + c - w) * per)) : (int)n - 1;
+    int prev = __shfl_up(unit, 1, 64);
+    if (lane == 0) prev = last;
+    for (int v = prev + 1; v <= unit; ++v) T.unit_start[s + v] = (int32_t)(k < len ? k : len);
+    last = __shfl(unit, 63, 64);
+    before += __shfl(c, 63, 64);
+  }
+  for (int64_t v = last + 1 + lane; v < n; v += 64) T.unit_start[s + v] = (int32_t)len;
 }
 
 // Whether the launch splits its walk (SPLIT of pairs_sum): the second queue pays where a pair's
@@ -167,11 +288,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LS == 
   __shared__ int bq[64 * 4];
   __shared__ int qk[LS == FDTBX_LINESHAPE_HOSEMANN ? 128 * 4 : 1];  // node indices (support edge)
   const int wv = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
-  const int64_t U = T.meta[1];
-  const int64_t total = U > 0 ? min(T.meta[0], T.max_units) : 0;
+  const int64_t total = min(T.meta[0], T.max_units);
   for_units(T, total, [&](int64_t u) {
     int64_t p0, p1;
-    const int t = unit_range(q, T, offsets, u, U, &p0, &p1);
+    const int t = unit_range(q, T, offsets, u, total, &p0, &p1);
     if (t < 0) return;
     const TilePixel px = tile_pixel(q, pix, tile, t, lane);
     unsigned long long cnt = 0;
@@ -191,8 +311,7 @@ __global__ void __launch_bounds__(64) k_unit_reduce(ProfParams q, UnitTable T, c
   if (t < 0) return;  // uniform
   const int lane = (int)threadIdx.x;
   const TilePixel px = tile_pixel(q, pix, tile, t, lane);
-  const int64_t U = T.meta[1];
-  const int64_t n = U > 0 ? ceil_div_dev(offsets[t + 1] - offsets[t], U) : 0, s = T.qscan[queue_pos(b, T.nj)];
+  const int64_t n = units_at(T, queue_pos(b, T.nj)), s = T.qscan[queue_pos(b, T.nj)];
   const int64_t n_in = s < 0 ? 0 : (s + n < T.max_units ? n : T.max_units - s);  // within the capacity
   float acc = 0.0f;
 #pragma unroll 8
@@ -424,15 +543,16 @@ int launch_balanced(const fdtbx_model* model, const float* refl, const float* no
   if (ws_bytes < L.total) return fail(FDTBX_ERR_BUFFER_TOO_SMALL, "balanced profile workspace too small");
   if (L.max_units >= (int64_t{1} << 31) || L.n_slots >= (int64_t{1} << 31))
     return fail(FDTBX_ERR_UNSUPPORTED, "balanced profile: too many units or tiles");
-  const UnitTable T = unit_view(L, order, model->geom.unit_pairs, ws);
+  UnitTable T = unit_view(L, order, model->geom.unit_pairs, ws);
+  T.weigh_most = weigh_most(q, model->geom.unit_pairs);
   float* partials = (float*)((char*)ws + L.partials);
   const int64_t n_tiles = (int64_t)q.tiles_x * q.tiles_y;
-  const unsigned gp = (unsigned)ceil_div(kXcds * L.nj, 256);
-  hipLaunchKernelGGL(k_unit_count, dim3(gp), dim3(256), 0, s, q, T, offsets, n_tiles);
-  FDTBX_LAUNCH_CHECK("balanced profile: unit count");
-  hipLaunchKernelGGL(k_scan_inplace, dim3(1), dim3(1024), 0, s, T.qscan, kXcds * L.nj, T.meta);
+  const unsigned gp = (unsigned)ceil_div(kXcds * L.nj, 4);
+  hipLaunchKernelGGL(k_unit_weight, dim3(gp), dim3(256), 0, s, q, T, offsets, n_tiles, refl, nodes, tile, idx);
+  FDTBX_LAUNCH_CHECK("balanced profile: unit weights");
+  hipLaunchKernelGGL(k_unit_scan, dim3(1), dim3(1024), 0, s, T, offsets, n_tiles);
   FDTBX_LAUNCH_CHECK("balanced profile: unit scan");
-  hipLaunchKernelGGL(k_unit_fill, dim3(gp), dim3(256), 0, s, q, T, offsets);
+  hipLaunchKernelGGL(k_unit_fill, dim3(gp), dim3(256), 0, s, q, T, offsets, n_tiles, refl, nodes, tile, idx);
   FDTBX_LAUNCH_CHECK("balanced profile: unit fill");
   auto launch = [&](auto units) { return units(q, refl, nodes, pix, tile, offsets, idx, T, partials, s); };
   const bool split = q.n >= kSplitNodes;

@@ -453,19 +453,21 @@ constexpr int kQueues = 64, kQueueStride = 32;
 constexpr size_t kQueueBytes = (size_t)kQueues * kQueueStride * sizeof(int32_t);
 
 // ---------------------------------------------------------------- work units of the balanced launches
-// The launched tiles' lists cut into units of at most U pairs (see fdtbx_profile_balanced).
-// Queue-major position of slot b: (b % 8) nj + b / 8, nj = ceil(n_slots / 8).  qscan holds the
-// units per position, then (after k_scan_inplace) the first unit of each position; queue x
-// spans the units qscan[x nj] .. qscan[(x + 1) nj] (the total for the last queue).
+// The launched tiles' lists cut into units (see fdtbx_profile_balanced).  Queue-major position of
+// slot b: (b % 8) nj + b / 8, nj = ceil(n_slots / 8).  qscan holds the first unit of each
+// position; XCD x's slots span the units qscan[x nj] .. qscan[(x + 1) nj] (the total for the last).
 struct UnitTable {
   const int32_t* order;  // tile of each slot, or null: the plain per-tile grid (tile_of_block)
   int64_t n_slots, nj;
   int64_t max_units;     // capacity of unit_slot and of the partial sums
   int64_t fixed_U;       // pairs per unit, or 0: chosen from the pair count (default_unit_pairs)
-  int64_t* qscan;        // [8 nj]
-  int64_t* meta;         // [0]: total units, [1]: pairs per unit
+  int64_t weigh_most;    // lists of at most this many pairs are cut by weight (forward launch)
+  int64_t* qscan;        // [8 nj] first unit of each position
+  int64_t* weight;       // [8 nj] weight of each position's list
+  int64_t* meta;         // [0]: total units, [1]: pairs per unit (of the mean weight)
   int32_t* ctr;          // [kQueues][kQueueStride] queue counters (the first int of each line)
   int32_t* unit_slot;    // [max_units] slot of each unit
+  int32_t* unit_start;   // [max_units] its first pair in the slot's list
 };
 
 __host__ __device__ inline int64_t queue_pos(int64_t b, int64_t nj) { return (b % kXcds) * nj + b / kXcds; }
@@ -478,23 +480,27 @@ __device__ inline int slot_tile(const ProfParams& q, const UnitTable& T, int64_t
 // Workspace of the balanced launch: the unit tables and the partial sums.
 struct UnitLayout {
   int64_t n_slots, nj, max_units;
-  size_t qscan, meta, ctr, unit_slot, partials, total;
+  size_t qscan, weight, meta, ctr, unit_slot, unit_start, partials, total;
 };
 
 inline UnitLayout unit_layout(const ProfParams& q, bool has_order, int64_t pair_cap, int64_t fixed_U) {
   UnitLayout L;
   L.n_slots = has_order ? order_grid(q.lcols, q.lrows) : tile_grid(q);
   L.nj = ceil_div(L.n_slots, kXcds);
-  // sum over tiles of ceil(len / U) <= pair_cap / U + n_slots
+  // sum over tiles of ceil(weight / W) <= total weight / W + n_slots <= pair_cap / U + n_slots
   L.max_units = (fixed_U > 0 ? ceil_div(pair_cap, fixed_U) : most_units(pair_cap)) + L.n_slots;
   size_t o = 0;
   L.qscan = o;
+  o += align_up((size_t)(kXcds * L.nj) * sizeof(int64_t), 256);
+  L.weight = o;
   o += align_up((size_t)(kXcds * L.nj) * sizeof(int64_t), 256);
   L.meta = o;
   o += 256;
   L.ctr = o;
   o += kQueueBytes;
   L.unit_slot = o;
+  o += align_up((size_t)L.max_units * sizeof(int32_t), 256);
+  L.unit_start = o;
   o += align_up((size_t)L.max_units * sizeof(int32_t), 256);
   L.partials = o;
   o += align_up((size_t)L.max_units * 64 * sizeof(float), 256);
@@ -503,20 +509,22 @@ inline UnitLayout unit_layout(const ProfParams& q, bool has_order, int64_t pair_
 }
 
 
-// Unit u's tile and pair range [*p0, *p1), or -1 when the tables do not describe such a unit
-// (only tables that a launch over other lists left behind would fail these checks; they keep
-// every read in bounds).
+// Unit u's tile and pair range [*p0, *p1) (which may be empty: a heavy pair can take the share
+// of several units), or -1 when the tables do not describe such a unit (only tables that a launch
+// over other lists left behind would fail these checks; they keep every read in bounds).
 __device__ inline int unit_range(const ProfParams& q, const UnitTable& T, const int64_t* __restrict__ offsets,
-                                 int64_t u, int64_t U, int64_t* p0, int64_t* p1) {
+                                 int64_t u, int64_t total, int64_t* p0, int64_t* p1) {
   const int64_t b = T.unit_slot[u];
   if (b < 0 || b >= T.n_slots) return -1;
   const int t = slot_tile(q, T, b);
   if (t < 0) return -1;
-  const int64_t k = u - T.qscan[queue_pos(b, T.nj)];
-  const int64_t a = offsets[t] + k * U, e = offsets[t + 1];
-  if (k < 0 || a >= e) return -1;
+  const int64_t o = offsets[t], e = offsets[t + 1];
+  const int64_t a = o + T.unit_start[u];
+  int64_t z = e;
+  if (u + 1 < total && T.unit_slot[u + 1] == b) z = min64(e, o + T.unit_start[u + 1]);
+  if (a < o || a > z) return -1;
   *p0 = a;
-  *p1 = a + U < e ? a + U : e;
+  *p1 = z;
   return t;
 }
 
@@ -593,10 +601,13 @@ inline UnitTable unit_view(const UnitLayout& L, const int32_t* order, int64_t fi
   T.nj = L.nj;
   T.max_units = L.max_units;
   T.fixed_U = fixed_U;
+  T.weigh_most = -1;
   T.qscan = (int64_t*)(w + L.qscan);
+  T.weight = (int64_t*)(w + L.weight);
   T.meta = (int64_t*)(w + L.meta);
   T.ctr = (int32_t*)(w + L.ctr);
   T.unit_slot = (int32_t*)(w + L.unit_slot);
+  T.unit_start = (int32_t*)(w + L.unit_start);
   return T;
 }
 
