@@ -416,7 +416,7 @@ __global__ void __launch_bounds__(kSAThreads) k_sf_adj_partial(SAParams p, const
       for (int i = 0; i < cnt; ++i) {
         const ReflLds q = rl[i];
         const double ph = fma((double)q.h, ax, fma((double)q.k, ay, (double)q.l * az));
-        const float fr = (float)(ph - floor(ph));
+        const float fr = (float)(ph - rint(ph));
         const float amp = ft[i][ta] * __builtin_amdgcn_exp2f(nBl2e * q.s2);
         const float cs = __builtin_amdgcn_cosf(fr), sn = __builtin_amdgcn_sinf(fr);
         // C t/occ with C = dF2 F*: real and imaginary parts
@@ -628,7 +628,7 @@ __global__ void __launch_bounds__(kSAThreads) k_b_sf_adj(const fdtbx_batch_entry
       for (int i = 0; i < cnt; ++i) {
         const ReflLds q = rl[i];
         const double ph = fma((double)q.h, ax, fma((double)q.k, ay, (double)q.l * az));
-        const float fr = (float)(ph - floor(ph));
+        const float fr = (float)(ph - rint(ph));
         const float amp = ft[i][ta] * __builtin_amdgcn_exp2f(nBl2e * q.s2);
         const float cs = __builtin_amdgcn_cosf(fr), sn = __builtin_amdgcn_sinf(fr);
         const float re = amp * (q.cre * cs - q.cim * sn);

@@ -5,7 +5,7 @@
 // range is split over gridDim.y so that small reflection lists still fill the chip.
 // The phase h x + k y + l z is formed in binary64 (exact: integer times float32),
 // reduced modulo one turn there and only then rounded to float32, so the argument
-// of the hardware sine/cosine (which take revolutions) carries ~3e-8 turns of error
+// of the hardware sine/cosine (which take revolutions) carries ~1.5e-8 turns of error
 // whatever the size of h.  The sums of each atom chunk are reduced in a fixed order
 // in binary64: deterministic, no atomics.
 //
@@ -13,11 +13,12 @@
 // mate of reflection i, so a block of the first half writes the second half's sums too after it
 // has compared the indices; where a block's mates are not mates, it evaluates them as well.
 //
-// Bound: the vector instructions of a term, 5 binary64 ones of 5 cycles per wave and SIMD, 3
-// transcendentals of 8.4 and 7 float32 ones of 2.6, or 68 cycles; 70 are reached.  The inner
-// loop reads the coordinates from LDS as binary64, converted once per atom and block, and
-// reduces the phase by v_fract_f64 alone (with a floor and a subtraction 7 % more).
-// 293298 reflections of 50000 atoms take 3.2 ms, 6.4 when every reflection was evaluated.
+// Bound: the vector instructions of a term, 6 binary64 ones of 5 cycles per wave and SIMD, 3
+// transcendentals of 8.4 and 7 float32 ones of 2.6, or 73 cycles; 73 are reached.  The inner
+// loop reads the coordinates from LDS as binary64, converted once per atom and block.
+// 293298 reflections of 50000 atoms take 3.4 ms, 6.4 when every reflection was evaluated; one
+// binary64 operation less, the phase's fraction in [0, 1) by v_fract_f64, takes 3.2 ms, but the
+// gradients of a small refinement step are then a fifth further off.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -29,7 +30,7 @@ namespace fdtbx {
 static constexpr int kSFThreads = 256;
 static constexpr int kMaxTypes = 16;
 // Atoms summed in float32 before they are added in binary64.  The float32 sums of a whole chunk
-// were most of the error: 1.7e-7 to 6.4e-7 of |F| for 160 to 30000 atoms, 1.1e-7 so.
+// were most of the error: 1.7e-7 to 6.4e-7 of |F| for 160 to 30000 atoms, 1.0e-7 to 1.6e-7 so.
 static constexpr int kSFGroup = 8;
 static_assert(kSFThreads % kSFGroup == 0, "a partly filled group of atoms ends inside the LDS array");
 static constexpr int64_t kSFBlocks = 2048;  // two rounds of the chip's 256 compute units at four blocks each
@@ -64,9 +65,11 @@ struct AtomsLds {
   }
 };
 
-// One term: h x + k y + l z modulo one turn, and its amplitude.
+// The phase of a term, h x + k y + l z to the nearest turn: at most half a turn either way, so that
+// its float32 rounding is half that of a phase in [0, 1).
 __device__ __forceinline__ float sf_phase(double h, double k, double l, double2 xy, double z) {
-  return (float)__builtin_amdgcn_fract(fma(h, xy.x, fma(k, xy.y, l * z)));
+  const double ph = fma(h, xy.x, fma(k, xy.y, l * z));
+  return (float)(ph - rint(ph));
 }
 
 __device__ __forceinline__ float form_factor(const float* c, double s2) {
@@ -247,8 +250,8 @@ int launch_batch_sf(const fdtbx_batch_entry* ent, const int64_t* blocks, int64_t
 }
 
 // Reflections per thread, atom chunks and their length.  Two reflections per thread share the
-// atom's LDS reads (293298 reflections of 50000 atoms: 3.4 ms against 3.7 with one, whose 40
-// bytes a term keep the LDS busy longer than the vector unit; four give 3.3), but a chunk then
+// atom's LDS reads (293298 reflections of 50000 atoms: 8 % less time than with one, whose 40
+// bytes a term keep the LDS busy longer than the vector unit; four gain another 2 %), but a chunk then
 // starts with twice the form factors, so they are taken where chunks of 1024 atoms fill the chip
 // (9692 reflections of 50000 atoms: 0.20 ms with one, 0.26 with two).
 static int sf_split(int64_t n_hkl, int64_t n_atoms, int32_t* n_chunks, int64_t* chunk) {
