@@ -341,6 +341,15 @@ __device__ static inline void window_node(int wi, int nw1, float inv_nw1, int* i
 // the FDTBX_NODE_BLOCK^2 node blocks that overlap them.
 constexpr int kPlainScanMax = 192;
 
+// Node k's offsets e_a and its weight omega, (e_0, e_1, e_2, omega).
+__device__ __forceinline__ float4 node_offsets(const float* __restrict__ nodes, int k, const float* Bv, const float* G1,
+                                               const float* G2) {
+  const float4 nd = *(const float4*)(nodes + (int64_t)FDTBX_NODE_FLOATS * k);
+  return make_float4(fmaf(nd.x, Bv[0], fmaf(nd.y, G1[0], nd.z * G2[0])),
+                     fmaf(nd.x, Bv[1], fmaf(nd.y, G1[1], nd.z * G2[1])),
+                     fmaf(nd.x, Bv[2], fmaf(nd.y, G1[2], nd.z * G2[2])), nd.w);
+}
+
 // Candidate nodes of one (tile, reflection) pair: the nodes k of window w whose offsets
 // e_a = B_a (c - 1) + G1_a c d1 + G2_a c d2 lie in [lo_a, hi_a] for a = 0, 1, 2.  Calls
 // sink(keep, k, e) on every lane of the wave with uniform control flow, 64 candidates a
@@ -353,11 +362,7 @@ __device__ __forceinline__ void scan_window(const ProfParams& q, const float* __
                                             const float* hi, int* bq, Sink&& sink) {
   const int lane = threadIdx.x & 63;
   auto node_e = [&](int k, float4* e) {
-    const float4 nd = *(const float4*)(nodes + (int64_t)FDTBX_NODE_FLOATS * k);
-    e->x = fmaf(nd.x, Bv[0], fmaf(nd.y, G1[0], nd.z * G2[0]));
-    e->y = fmaf(nd.x, Bv[1], fmaf(nd.y, G1[1], nd.z * G2[1]));
-    e->z = fmaf(nd.x, Bv[2], fmaf(nd.y, G1[2], nd.z * G2[2]));
-    e->w = nd.w;
+    *e = node_offsets(nodes, k, Bv, G1, G2);
     return e->x >= lo[0] && e->x <= hi[0] && e->y >= lo[1] && e->y <= hi[1] && e->z >= lo[2] && e->z <= hi[2];
   };
   const int nw1 = w.i1hi - w.i1lo + 1;

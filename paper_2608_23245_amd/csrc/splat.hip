@@ -20,9 +20,9 @@
 // Mapping: one 64-lane wave per (reflection, radial sample) walks the n_s x n_s tangent
 // samples in 8x8 patches, one sample per lane.  Per patch the wave bounds the node window
 // from the samples' own coordinates, queues the nodes whose offsets can reach some
-// sample (the same block test, queue and walk as the profile kernel), evaluates I(S) per
-// lane and deposits with float atomics.  Sample positions and the projection are binary64
-// without fused multiply-adds (this file is compiled with -ffp-contract=off), so the pixel
+// sample (the same block test, queue and walk as the profile kernel), or lets every lane walk its
+// own nodes (kLaneWindow), evaluates I(S) per lane and deposits with float atomics.  Sample
+// positions and the projection are binary64 without fused multiply-adds (this file is compiled with -ffp-contract=off), so the pixel
 // each sample lands in is reproducible bit for bit.
 #include <hip/hip_runtime.h>
 
@@ -58,10 +58,11 @@ __device__ static inline void splat_pixels(const SplatParams& p, const double* S
   // t k_out . n = SF cos d; its detector coordinates are y = SF k_y cos d / D, z = SF k_z / D
   const double D = kx * p.cd + sz * p.sd;
   if (!(D > 0.0)) return;
+  // k_y = +-S_y: products and quotients of a negated operand are exact negatives
+  const double y = p.SF * sy * p.cd / D, z = p.SF * sz / D;
+  const double u = y / p.pixel, fj = floor(z / p.pixel + p.cy);
   for (int b = 0; b < 2; ++b) {
-    const double ky = b == 0 ? sy : -sy;
-    const double y = p.SF * ky * p.cd / D, z = p.SF * sz / D;
-    const double fi = floor(y / p.pixel + p.cx), fj = floor(z / p.pixel + p.cy);
+    const double fi = floor((b == 0 ? u : -u) + p.cx);
     if (fi >= 0.0 && fi < (double)p.W && fj >= 0.0 && fj < (double)p.H) out[b] = (int64_t)fj * p.W + (int64_t)fi;
   }
 }
@@ -97,6 +98,18 @@ __device__ __forceinline__ void walk_queue_edge_al(const ProfParams& q, const fl
   accr += fix;
 }
 
+// Where a patch is wide against the support, the wave's lanes walk their own nodes: its window
+// (at most kLaneWindow nodes, at least the queue's 128) goes to LDS as it lies, and each lane takes
+// the c1 x c2 nodes from the first of its own window on, c1 and c2 the most columns and rows of any
+// lane.  Of the shared queue's entries only one lane in forty was in reach at 32 samples and 24
+// nodes per side.  It pays where the lanes' nodes are at most half the patch's; the lanes' windows
+// are only formed where the support's reach in nodes leaves room for that.  Queue / this rule, 24
+// nodes, 16 and 32 samples per side: Gaussian 0.335 / 0.214 and 0.624 / 0.524 ms, Laue 0.397 /
+// 0.266 and 0.761 / 0.593, Hosemann 0.592 / 0.343 and 1.10 / 0.782; with 96 samples every patch
+// takes the queue (0.847 / 0.842).  With lanes up to the whole window that becomes 1.55 ms; windows
+// of up to 512 nodes gain nothing.
+constexpr int kLaneWindow = 256;
+
 template <bool COUNT, int LS>
 __global__ void __launch_bounds__(64) k_splat(SplatParams p, const int32_t* __restrict__ hkl, const float* __restrict__ refl,
                                               const float* __restrict__ nodes, float* __restrict__ image,
@@ -104,7 +117,7 @@ __global__ void __launch_bounds__(64) k_splat(SplatParams p, const int32_t* __re
   // the Hosemann support edge is decided in binary64 (walk_queue_edge_al): the queue then
   // carries its node indices in qk
   constexpr bool EDGE = LS == FDTBX_LINESHAPE_HOSEMANN && !COUNT;
-  __shared__ float4 qn[128];
+  __shared__ float4 qn[kLaneWindow];
   __shared__ int bq[64];
   __shared__ int qk[EDGE ? 128 : 1];
   const int lane = threadIdx.x & 63;
@@ -139,6 +152,7 @@ __global__ void __launch_bounds__(64) k_splat(SplatParams p, const int32_t* __re
   HoseK hk = {};
   if (LS == FDTBX_LINESHAPE_HOSEMANN && !COUNT) hose_constants(rec, hk);
   const float wk = f.at(RS_WK);
+  const float reach = 2.0f * q.inv_h * __builtin_amdgcn_rcpf(f.at(RS_R0));  // nodes across per support half-width
   unsigned long long cnt = 0;
 
   for (int t = 0; t < p.tiles_s * p.tiles_s; ++t) {
@@ -182,35 +196,76 @@ __global__ void __launch_bounds__(64) k_splat(SplatParams p, const int32_t* __re
     float accr = 0.0f;
     if (node_window_ranges(q, f.at(RS_R0), sl, sh, l1, h1, l2, h2, f.at(RS_RHO), f.at(RS_RHO + 1), f.at(RS_RHO + 2),
                            &w)) {
-      int qlen = 0;  // uniform
-      scan_window(q, nodes, w, Bv, G1, G2, lo, hi, bq, [&](bool keep, int k, float4 e) {
-        const unsigned long long bal = __ballot(keep);
-        if (keep) {
-          const int pos = qlen + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
-          qn[pos] = LS == FDTBX_LINESHAPE_LAUE ? tag_kappa4(e) : e;
-          if (EDGE) qk[pos] = k;
+      const int nw1 = w.i1hi - w.i1lo + 1, nw2 = w.i2hi - w.i2lo + 1;
+      // each lane's own window, and the number of columns and rows that hold the largest ones
+      Window v;
+      const float reach1 = fmaf(reach, f.at(RS_RHO + 1), 1.0f), reach2 = fmaf(reach, f.at(RS_RHO + 2), 1.0f);
+      const bool lanes = nw1 * nw2 <= kLaneWindow && 2.0f * reach1 * reach2 <= (float)(nw1 * nw2);  // uniform
+      const bool own = lanes && in && node_window_ranges(q, f.at(RS_R0), pS, pS, p1, p1, p2, p2, f.at(RS_RHO), f.at(RS_RHO + 1),
+                                                f.at(RS_RHO + 2), &v);
+      const int c1 = lanes ? min(nw1, wave_max_i32(own ? v.i1hi - v.i1lo + 1 : 0)) : nw1;
+      const int c2 = lanes ? min(nw2, wave_max_i32(own ? v.i2hi - v.i2lo + 1 : 0)) : nw2;
+      if (lanes && 2 * c1 * c2 <= nw1 * nw2) {
+        // the patch's nodes by their place in the window, and every lane's walk over the c1 c2
+        // nodes from its own first one (further ones fail the support test)
+        const float inv_nw1 = __builtin_amdgcn_rcpf((float)nw1);
+        for (int i = lane; i < nw1 * nw2; i += 64) {
+          int a1, a2;
+          window_node(i, nw1, inv_nw1, &a1, &a2);
+          const float4 e = node_offsets(nodes, (w.i2lo + a2) * q.n + (w.i1lo + a1), Bv, G1, G2);
+          qn[i] = LS == FDTBX_LINESHAPE_LAUE ? tag_kappa4(e) : e;
         }
-        qlen += __popcll(bal);
         wave_sync();
-        if (qlen >= 64) {
-          if (EDGE)
-            walk_queue_edge_al(q, qn, qk, 64, al, elo, ehi, hk, rec, al64, accr);
-          else
-            walk_queue<COUNT, LS>(qn, 64, al, q.half_m, hk, accr, cnt);
-          qlen -= 64;
-          wave_sync();
-          if (lane < qlen) {
-            qn[lane] = qn[64 + lane];
-            if (EDGE) qk[lane] = qk[64 + lane];
+        const int f1 = own ? min(max(v.i1lo - w.i1lo, 0), nw1 - c1) : 0;
+        const int f2 = own ? min(max(v.i2lo - w.i2lo, 0), nw2 - c2) : 0;
+        float part = 0.0f;
+        for (int a2 = 0; a2 < c2; ++a2)
+          for (int a1 = 0; a1 < c1; ++a1) {
+            const float4 nd = qn[(f2 + a2) * nw1 + f1 + a1];
+            if (EDGE) {
+              const float ya = al[0] - nd.x, yb = al[1] - nd.y, yc = al[2] - nd.z;
+              const float mx = fmaxf(fmaxf(fabsf(ya), fabsf(yb)), fabsf(yc));
+              bool inside = mx <= elo;
+              if (hose_band(mx, elo, ehi))
+                inside = hose_inside64_al(q, rec, (w.i2lo + f2 + a2) * q.n + (w.i1lo + f1 + a1), al64);
+              if (inside) part = fmaf(nd.w, hose_prod(ya, yb, yc, hk), part);
+            } else {
+              eval_node<COUNT, LS>(nd, al[0], al[1], al[2], q.half_m, hk, part, cnt);
+            }
           }
+        accr = part;
+        wave_sync();
+      } else {
+        int qlen = 0;  // uniform
+        scan_window(q, nodes, w, Bv, G1, G2, lo, hi, bq, [&](bool keep, int k, float4 e) {
+          const unsigned long long bal = __ballot(keep);
+          if (keep) {
+            const int pos = qlen + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+            qn[pos] = LS == FDTBX_LINESHAPE_LAUE ? tag_kappa4(e) : e;
+            if (EDGE) qk[pos] = k;
+          }
+          qlen += __popcll(bal);
           wave_sync();
-        }
-      });
-      if (EDGE)
-        walk_queue_edge_al(q, qn, qk, qlen, al, elo, ehi, hk, rec, al64, accr);
-      else
-        walk_queue<COUNT, LS>(qn, qlen, al, q.half_m, hk, accr, cnt);
-      wave_sync();
+          if (qlen >= 64) {
+            if (EDGE)
+              walk_queue_edge_al(q, qn, qk, 64, al, elo, ehi, hk, rec, al64, accr);
+            else
+              walk_queue<COUNT, LS>(qn, 64, al, q.half_m, hk, accr, cnt);
+            qlen -= 64;
+            wave_sync();
+            if (lane < qlen) {
+              qn[lane] = qn[64 + lane];
+              if (EDGE) qk[lane] = qk[64 + lane];
+            }
+            wave_sync();
+          }
+        });
+        if (EDGE)
+          walk_queue_edge_al(q, qn, qk, qlen, al, elo, ehi, hk, rec, al64, accr);
+        else
+          walk_queue<COUNT, LS>(qn, qlen, al, q.half_m, hk, accr, cnt);
+        wave_sync();
+      }
     }
     if (!COUNT && in && accr != 0.0f) {
       int64_t px[2];
