@@ -41,15 +41,18 @@ constexpr int kJB = 8;
 // 2.88 / 0.29 / 0.18 / 0.18, 224x224 (784) 1.44 / 0.37 / 0.33 / 0.36, 384x384 (2304)
 // 4.06 / 2.29 / 1.74 / 1.79; 1024x1024 (16384) is better with one: 140 against 156 with four.
 // At most kCylMaxParts: a list of 64x64 pixels has few pairs, and sharing the ring blocks of a
-// pair repeats its setup (0.29 ms with 32 parts, 0.18 with 128).
+// pair repeats its setup (0.29 ms with 32 parts, 0.18 with 128).  (All measured with a longer
+// set-up of a block of ring indices, whose bounds came from every ring point; with those of the
+// arc's ends the chosen column is 0.18 / 0.29 / 1.30 ms and the 1024x1024 pixels take 123.)
 constexpr int64_t kCylTarget = 16384;
 constexpr int64_t kCylMaxParts = 128;
 
 // Waves per SIMD that k_cyl is compiled for.  Its walk is a chain of transcendentals per
-// evaluation, and the two waves that its 163 to 210 registers allowed left the SIMDs idle
-// between them: 300 reflections over 1024x1024 pixels take 167 ms at two, 140 at three and
-// 135 at four, which spills 12 to 68 registers outside the walk.
-constexpr int kCylOccupancy = 4;
+// evaluation, and the two waves that its 155 to 210 registers allowed left the SIMDs idle
+// between them.  224x224 / 384x384 pixels / 300 reflections over 1024x1024 at three, four and five
+// waves: Laue 0.295, 0.285, 0.289 / 1.36, 1.30, 1.34 / 129, 123, 123 ms; Gaussian 0.220, 0.202,
+// 0.224 / 1.11, 1.03, 1.07; Hosemann, which spills most, 0.379, 0.395, 0.456 / 1.78, 1.81, 2.18.
+__host__ __device__ constexpr int cyl_occupancy(int ls) { return ls == FDTBX_LINESHAPE_HOSEMANN ? 3 : 4; }
 
 // The queue walk of walk_queue, each entry evaluated at the lane's kJB ring points.
 template <bool COUNT, int LS>
@@ -123,7 +126,7 @@ __device__ __forceinline__ void walk_ring_edge(const ProfParams& q, const float4
 // (WAVES parts / G)-th block (its own LDS queue); wave 0 adds the others' pixel sums in wave
 // order, and k_cyl_sum the parts in part order, so the result does not depend on the launch.
 template <bool COUNT, int LS, int WAVES>
-__global__ void __launch_bounds__(64 * WAVES, kCylOccupancy) k_cyl(CylParams p, const float* __restrict__ refl,
+__global__ void __launch_bounds__(64 * WAVES, cyl_occupancy(LS)) k_cyl(CylParams p, const float* __restrict__ refl,
                                                     const float* __restrict__ nodes, const double* __restrict__ pix,
                                                     const int64_t* __restrict__ offsets, const int32_t* __restrict__ idx,
                                                     float* __restrict__ image, unsigned long long* __restrict__ counts,
@@ -159,6 +162,7 @@ __global__ void __launch_bounds__(64 * WAVES, kCylOccupancy) k_cyl(CylParams p, 
   const double dphi = 2.0 * M_PI / (double)n;
   const int ring_lo = -(n / 2), ring_hi = n - n / 2 - 1;
   const double cd = cos(dphi), sd = sin(dphi);
+  const float sag = (float)(R * (1.0 - cos(0.5 * (kJB - 1) * dphi)) * 1.0001);
   const int64_t p0 = offsets[t], p1 = offsets[t + 1];
   const int groups = p1 - p0 < p.parts ? (p1 > p0 ? (int)(p1 - p0) : 1) : p.parts;
   const int ring_parts = p.parts / groups;
@@ -240,51 +244,60 @@ __global__ void __launch_bounds__(64 * WAVES, kCylOccupancy) k_cyl(CylParams p, 
     }
     double cj = cos((double)(J0 + kJB * first) * dphi), sj = sin((double)(J0 + kJB * first) * dphi);
     const float fZ = (float)(Z - ZD), fz = (float)Z;
+    const float vz[3] = {tz[0] * fZ, tz[1] * fZ, tz[2] * fZ};
     float accp = 0.0f;
-    // kJB consecutive ring indices share one node window, queue and walk
+    // kJB consecutive ring indices share one node window, queue and walk.  With 64 lanes of
+    // eight points a block's set-up is a large part of its time, so its bounds come from the arc's
+    // ends alone (0.33 -> 0.29 ms at 224x224 pixels, 1.72 -> 1.30 at 384x384).
     for (int jb = J0 + kJB * first; jb <= J1; jb += kJB * stride) {
       float al[kJB][3];
-      float amin[3] = {INFINITY, INFINITY, INFINITY}, amax[3] = {-INFINITY, -INFINITY, -INFINITY};
-      float pmin[3] = {INFINITY, INFINITY, INFINITY}, pmax[3] = {-INFINITY, -INFINITY, -INFINITY};
+      // the ends of the block's arc: al and the coordinates along S, e1, e2
+      float ae[2][3], pe[2][3];
 #pragma unroll
       for (int u = 0; u < kJB; ++u) {
         const int jj = jb + u;
-        const bool act = has && jj >= jl && jj <= jh;
-        const float fX = (float)(R * cj - RD), fY = (float)(R * sj);
-        // the ring point's coordinates along S, e1, e2
-        const float Rc = (float)(R * cj), Rs = (float)(R * sj);
-        const float pv[3] = {fmaf(Rc, f.at(RS_CS), fmaf(Rs, az[0], fz * f.at(RS_CS + 1))),
-                             fmaf(Rc, f.at(RS_C1), fmaf(Rs, az[1], fz * f.at(RS_C1 + 1))),
-                             fmaf(Rc, f.at(RS_C2), fmaf(Rs, az[2], fz * f.at(RS_C2 + 1)))};
+        const bool act = jj >= jl && jj <= jh;  // jl > jh where the lane has no ring point in reach
+        const double X = R * cj, Y = R * sj;
+        const float fX = (float)(X - RD), fY = (float)Y;
+        float v[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-          const float v = fmaf(tr[a], fX, fmaf(ta[a], fY, tz[a] * fZ));
-          al[u][a] = act ? (LS == FDTBX_LINESHAPE_LAUE ? tag_alpha(v) : v) : 1.0e30f;
-          amin[a] = act ? fminf(amin[a], v) : amin[a];
-          amax[a] = act ? fmaxf(amax[a], v) : amax[a];
-          pmin[a] = act ? fminf(pmin[a], pv[a]) : pmin[a];
-          pmax[a] = act ? fmaxf(pmax[a], pv[a]) : pmax[a];
+          v[a] = fmaf(tr[a], fX, fmaf(ta[a], fY, vz[a]));
+          al[u][a] = LS == FDTBX_LINESHAPE_LAUE ? tag_alpha(v[a]) : v[a];
         }
-        const double cn = cj * cd - sj * sd;
-        sj = sj * cd + cj * sd;
+        al[u][0] = act ? al[u][0] : 1.0e30f;
+        if (u == 0 || u == kJB - 1) {
+          const int e = u ? 1 : 0;
+          const float Rc = (float)X;
+          pe[e][0] = fmaf(Rc, f.at(RS_CS), fmaf(fY, az[0], fz * f.at(RS_CS + 1)));
+          pe[e][1] = fmaf(Rc, f.at(RS_C1), fmaf(fY, az[1], fz * f.at(RS_C1 + 1)));
+          pe[e][2] = fmaf(Rc, f.at(RS_C2), fmaf(fY, az[2], fz * f.at(RS_C2 + 1)));
+#pragma unroll
+          for (int a = 0; a < 3; ++a) ae[e][a] = v[a];
+        }
+        const double cn = fma(cj, cd, -(sj * sd));
+        sj = fma(sj, cd, cj * sd);
         cj = cn;
       }
       if (stride > 1) {
-        const double cn = cj * cw - sj * sw;
-        sj = sj * cw + cj * sw;
+        const double cn = fma(cj, cw, -(sj * sw));
+        sj = fma(sj, cw, cj * sw);
         cj = cn;
       }
-      float lo[3], hi[3];
+      // a coordinate of the ring is a sinusoid of the azimuth: over an arc of half-angle d it stays
+      // within its amplitude times 1 - cos d of its values at the arc's ends
+      const bool reach = jb <= jh && jb + kJB > jl;
+      float lo[3], hi[3], pl[3], ph[3];
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
-        lo[a] = wave_min(amin[a]) - q.half_m - q.margin;
-        hi[a] = wave_max(amax[a]) + q.half_m + q.margin;
+        const float da = sag * (fabsf(tr[a]) + fabsf(ta[a]));
+        lo[a] = wave_min(reach ? fminf(ae[0][a], ae[1][a]) - da : INFINITY) - q.half_m - q.margin;
+        hi[a] = wave_max(reach ? fmaxf(ae[0][a], ae[1][a]) + da : -INFINITY) + q.half_m + q.margin;
+        pl[a] = wave_min(reach ? fminf(pe[0][a], pe[1][a]) - sag : INFINITY);
+        ph[a] = wave_max(reach ? fmaxf(pe[0][a], pe[1][a]) + sag : -INFINITY);
       }
-      const float sl = wave_min(pmin[0]), sh = wave_max(pmax[0]);
-      const float l1 = wave_min(pmin[1]), h1 = wave_max(pmax[1]);
-      const float l2 = wave_min(pmin[2]), h2 = wave_max(pmax[2]);
       Window w;
-      if (node_window_ranges(q, r0, sl, sh, l1, h1, l2, h2, rS, r1, r2, &w)) {
+      if (node_window_ranges(q, r0, pl[0], ph[0], pl[1], ph[1], pl[2], ph[2], rS, r1, r2, &w)) {
         float accr = 0.0f;
         int qlen = 0;  // uniform
         scan_window(q, nodes, w, Bv, G1, G2, lo, hi, bq, [&](bool keep, int k, float4 e) {
