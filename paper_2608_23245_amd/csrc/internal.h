@@ -45,6 +45,11 @@ inline int32_t lcols_of(const fdtbx_geometry* g) { return (g->mirror & 1) ? (til
 inline int32_t lrows_of(const fdtbx_geometry* g) { return (g->mirror & 2) ? (tiles_y_of(g) + 1) / 2 : tiles_y_of(g); }
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// Groups of threads that share the terms of a thread's sum in the batched structure factors and
+// their adjoint, for n blocks of 256 sums each: a batch of a few small models has tens of blocks,
+// far fewer than the card holds, and each thread's chain of terms is its time.
+inline int batch_split(int64_t n) { return n <= 64 ? 16 : (n <= 256 ? 4 : 1); }
+
 // v[0..n) = x, by a kernel (hipMemsetAsync nodes do not belong in captured graphs).
 template <class T>
 __global__ void k_fill(T* __restrict__ v, int64_t n, T x) {
