@@ -301,22 +301,28 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LS == 
   });
 }
 
-// Per launched tile: its units' pixel sums added in unit order, times the Lorentz factor,
-// written with the mirror folds.
-__global__ void __launch_bounds__(64) k_unit_reduce(ProfParams q, UnitTable T, const double* __restrict__ pix,
-                                                    const double* __restrict__ tile, const int64_t* __restrict__ offsets,
-                                                    const float* __restrict__ partials, float* __restrict__ image) {
+// Per launched tile: its units' pixel sums, times the Lorentz factor, written with the mirror
+// folds.  Four waves share a tile, wave w adding the units w, w + 4, ... in order and wave 0 the
+// four sums: a tile of few pairs each has many units, and one wave waited for every eight of them
+// (64 tiles of 37 units in the mean 20 -> 7 us, 4096 of 130 units 108 -> 39 us).
+__global__ void __launch_bounds__(256) k_unit_reduce(ProfParams q, UnitTable T, const double* __restrict__ pix,
+                                                     const double* __restrict__ tile, const float* __restrict__ partials,
+                                                     float* __restrict__ image) {
+  __shared__ float sum[3][64];
   const int64_t b = blockIdx.x;
   const int t = slot_tile(q, T, b);
   if (t < 0) return;  // uniform
-  const int lane = (int)threadIdx.x;
+  const int lane = (int)threadIdx.x & 63, wv = (int)threadIdx.x >> 6;
   const TilePixel px = tile_pixel(q, pix, tile, t, lane);
   const int64_t n = units_at(T, queue_pos(b, T.nj)), s = T.qscan[queue_pos(b, T.nj)];
   const int64_t n_in = s < 0 ? 0 : (s + n < T.max_units ? n : T.max_units - s);  // within the capacity
   float acc = 0.0f;
 #pragma unroll 8
-  for (int64_t k = 0; k < n_in; ++k) acc += partials[(s + k) * 64 + lane];  // a tile of few pairs each has many units
-  if (!px.in) return;
+  for (int64_t k = wv; k < n_in; k += 4) acc += partials[(s + k) * 64 + lane];
+  if (wv > 0) sum[wv - 1][lane] = acc;
+  __syncthreads();
+  if (wv > 0 || !px.in) return;
+  acc = (acc + sum[0][lane]) + (sum[1][lane] + sum[2][lane]);
   write_folded(q, image, px.i, px.j, px.tx, px.ty, (float)(q.delta / (px.R + q.delta)) * acc);
 }
 
@@ -564,8 +570,8 @@ int launch_balanced(const fdtbx_model* model, const float* refl, const float* no
   else
     rc = split ? launch(launch_units<FDTBX_LINESHAPE_LAUE, true>) : launch(launch_units<FDTBX_LINESHAPE_LAUE, false>);
   if (rc) return rc;
-  hipLaunchKernelGGL(k_unit_reduce, dim3((unsigned)L.n_slots), dim3(64), 0, s, q, T, pix, tile, offsets,
-                     (const float*)partials, image);
+  hipLaunchKernelGGL(k_unit_reduce, dim3((unsigned)L.n_slots), dim3(256), 0, s, q, T, pix, tile, (const float*)partials,
+                     image);
   FDTBX_LAUNCH_CHECK("balanced profile: reduce");
   return FDTBX_OK;
 }
