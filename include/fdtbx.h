@@ -677,7 +677,7 @@ int fdtbx_pattern_backward_noalloc(const fdtbx_model* model, const int32_t* hkl,
  *   model_rb[n_models+1]: first refl_blocks entry of each model;
  *   atom_blocks: blocks of 256 atoms;  node_blocks: blocks of 256 node-table rows
  *               (fdtbx_node_rows(n_nodes) rows per model: node and block records);
- *   tile_items: (model, tile) pairs in the order the persistent kernels take them
+ *   tile_items: (model, tile) pairs in the order the kernels start them
  *               (longest culling list first balances the tail). */
 typedef struct fdtbx_batch_entry {
   fdtbx_model model;
@@ -720,7 +720,7 @@ int fdtbx_batch_set_globals(fdtbx_batch_entry* entries, int32_t n_models, const 
 
 /* Forward step for all models: structure factors F [sum n_hkl][2] and F2, reflection
  * records, node tables, and the images (float32, each [height][width] at pix_off).
- * counter: device int64 [2] scratch for the persistent kernel's work queue. */
+ * counter: device int64 [2] scratch (the work queue of the per-tile forward). */
 int fdtbx_batch_forward(const fdtbx_batch_entry* entries, int32_t n_models, const int64_t* refl_blocks, int64_t n_rb,
                         const int64_t* node_blocks, int64_t n_nb, const int64_t* tile_items, int64_t n_items,
                         const int32_t* hkl, const float* x, const float* y, const float* z, const float* B,

@@ -19,7 +19,7 @@ launch is too short for its time to say anything about their work).  Choices are
 model (every model field except tile_w, and the reflection count) behind a lock, so a
 refinement loop tunes once.
 
-A batch (batch.py) runs the tiles of all its models in one persistent launch, so the
+A batch (batch.py) runs the tiles of all its models in one launch, so the
 quantity to tune there is the batched forward's time, not each model's own launch:
 tune_batch builds the batch in each candidate shape and keeps the fastest engine.
 

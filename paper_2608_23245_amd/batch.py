@@ -150,7 +150,7 @@ class BatchEngine:
                       "z": dev(np.concatenate(az), torch.float32), "B": dev(np.concatenate(aB), torch.float32),
                       "occ": dev(np.concatenate(aocc), torch.float32), "type": dev(np.concatenate(atype), torch.int32),
                       "ff": dev(np.concatenate(ffs), torch.float32)}
-        # longest culling list first: the persistent kernels take items in this order
+        # longest culling list first: the kernels start items in this order
         cost = np.concatenate(costs)
         order = np.argsort(-cost, kind="stable")
         self.items = dev(np.asarray(items, dtype=np.int64)[order], torch.int64)
