@@ -377,7 +377,7 @@ int fdtbx_profile(const fdtbx_model* model, const float* refl, const float* node
  *   ws        device workspace of fdtbx_profile_balanced_workspace(model, pair_cap) bytes:
  *             about 264 bytes per unit, for max(min(8192, pair_cap), min(2^15, ceil(pair_cap /
  *             16)), min(2^19, ceil(pair_cap / 32))) units plus one per tile when unit_pairs is 0
- *             (at most 136 MB besides the tiles), ceil(pair_cap / unit_pairs) plus one per tile
+ *             (at most 139 MB besides the tiles), ceil(pair_cap / unit_pairs) plus one per tile
  *             otherwise
  * fdtbx_unit_pairs(n): the library's pairs per unit for n culled pairs, max(min(16,
  * ceil(n / 8192)), min(32, ceil(n / 2^15)), ceil(n / 2^19)) (32 for n = 0, 0 for n < 0). */

@@ -553,7 +553,7 @@ int launch_balanced(const fdtbx_model* model, const float* refl, const float* no
   if (L.max_units >= (int64_t{1} << 31) || L.n_slots >= (int64_t{1} << 31))
     return fail(FDTBX_ERR_UNSUPPORTED, "balanced profile: too many units or tiles");
   UnitTable T = unit_view(L, order, model->geom.unit_pairs, ws);
-  T.weigh_most = weigh_most(q, model->geom.unit_pairs);
+  T.weigh_most = min64(weigh_most(q, model->geom.unit_pairs), pair_cap);  // more pairs than idx holds are not read
   float* partials = (float*)((char*)ws + L.partials);
   const int64_t n_tiles = (int64_t)q.tiles_x * q.tiles_y;
   const unsigned gp = (unsigned)ceil_div(kXcds * L.nj, 4);
