@@ -364,7 +364,7 @@ int fdtbx_profile(const fdtbx_model* model, const float* refl, const float* node
 /* fdtbx_profile_balanced: the image of fdtbx_profile (the same sum, Eqs. direct_sum and
  * lorentz) from a launch balanced over the compute units.  The launched tiles' lists are cut
  * into work units of geom.unit_pairs pairs; 0: of fdtbx_unit_pairs(n_pairs) pairs (read on the
- * device from offsets[n_tiles]), or from 8193 to 4 n_nodes^4 pairs, of as many pairs of mean
+ * device from offsets[n_tiles]), or from 8193 to 2048 n_nodes^2 pairs, of as many pairs of mean
  * weight, a pair's weight being an estimate of its time from its node window.  Persistent waves take the
  * units from queues, eight for each XCD (slot b of the launch order feeds those of XCD b % 8, in
  * slot order), each unit writes its 64 pixel sums to a slot of its own, and a second kernel adds

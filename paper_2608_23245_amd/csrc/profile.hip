@@ -137,16 +137,13 @@ __device__ inline int pair_weight(const ProfParams& q, const float* __restrict__
 // hundredfold: a low-order reflection has every node in reach of a tile, most have a few.  Cut
 // by their number alone, single units of heavy pairs ran on for 40 % of a launch of 490,639
 // Hosemann pairs after the median wave had finished.  Weighing reads every pair's record twice,
-// 30 to 40 us per million pairs, and what it saves grows with the nodes of a heavy pair.  Forward
+// about 40 us per million pairs, and what it saves grows with the nodes of a heavy pair.  Forward
 // + adjoint, cut by number / by weight, at 16 nodes per side: 28,657 pairs 0.120 + 0.148 / 0.109 +
 // 0.117 ms, 485,808 pairs 0.378 + 0.632 / 0.391 + 0.539, 1.8 million 0.754 + 1.356 / 0.848 +
-// 1.204, 7.2 million 2.36 + 4.37 / 2.65 + 4.22; at 32: 28.9 million 16.3 + 32.7 / 17.1 + 32.3; at
-// 64: 28,657 pairs 1.10 + 1.92 / 0.83 + 1.42, 485,808 pairs 3.60 + 7.63 / 2.92 + 6.17, 7.2 million
-// 22.4 + 49.1 / 21.7 + 46.4, 28.9 million 50.4 + 106 / 49.9 + 103.5, 40.3 million 78.1 + 166 /
-// 76.6 + 161.
+// 1.204, 7.2 million 2.36 + 4.37 / 2.65 + 4.22; at 64 nodes: 28,657 pairs 1.10 + 1.92 / 0.83 +
+// 1.42, 485,808 pairs 3.60 + 7.63 / 2.92 + 6.17, 7.2 million 22.4 + 49.1 / 21.7 + 46.4.
 static int64_t weigh_most(const ProfParams& q, int64_t fixed_U) {
-  const int64_t nodes = (int64_t)q.n * q.n;
-  return fixed_U > 0 ? -1 : 4 * nodes * nodes;  // 2^18 pairs at 16 nodes per side, 2^26 at 64
+  return fixed_U > 0 ? -1 : (int64_t)q.n * q.n * 2048;  // 2^19 pairs at 16 nodes per side, 2^23 at 64
 }
 // Up to 8192 pairs a unit is one pair whatever its weight.
 __device__ inline bool weighed(const UnitTable& T, int64_t n_pairs) { return n_pairs > kUnitFew && n_pairs <= T.weigh_most; }
