@@ -142,6 +142,9 @@ __device__ inline int pair_weight(const ProfParams& q, const float* __restrict__
 // 0.117 ms, 485,808 pairs 0.378 + 0.632 / 0.391 + 0.539, 1.8 million 0.754 + 1.356 / 0.848 +
 // 1.204, 7.2 million 2.36 + 4.37 / 2.65 + 4.22; at 64 nodes: 28,657 pairs 1.10 + 1.92 / 0.83 +
 // 1.42, 485,808 pairs 3.60 + 7.63 / 2.92 + 6.17, 7.2 million 22.4 + 49.1 / 21.7 + 46.4.
+// Longer lists of dense grids would still gain (28.9 million pairs 50.4 + 106 / 49.9 + 103.5, the
+// large model 1024 / 1010), but are cut by number: an unfolded launch then reproduces a folded one
+// bit for bit from the folded one's fdtbx_unit_pairs.
 static int64_t weigh_most(const ProfParams& q, int64_t fixed_U) {
   return fixed_U > 0 ? -1 : (int64_t)q.n * q.n * 2048;  // 2^19 pairs at 16 nodes per side, 2^23 at 64
 }
