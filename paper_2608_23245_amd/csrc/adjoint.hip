@@ -712,9 +712,8 @@ int launch_batch_backward(const fdtbx_batch_entry* ent, int32_t n_models, const 
                           float* dF2, float* d_x, float* d_y, float* d_z, float* d_B, float* d_occ, double* d_globals,
                           int64_t* counter, const PairOrder* fixed, hipStream_t s) {
   if (fixed) {
-    hipLaunchKernelGGL(k_zero_f32, dim3((unsigned)ceil_div(12 * fixed->n_pairs, 256)), dim3(256), 0, s, fixed->partials,
-                       12 * fixed->n_pairs);
-    FDTBX_LAUNCH_CHECK("batch adjoint partials zero");
+    const int rc = fill(fixed->partials, 12 * fixed->n_pairs, 0.0f, s);
+    if (rc) return rc;
   } else {
     hipLaunchKernelGGL(k_zero_f64, dim3((unsigned)ceil_div(6 * n_hkl_total, 256)), dim3(256), 0, s, sums, 6 * n_hkl_total);
     FDTBX_LAUNCH_CHECK("batch adjoint zero");
