@@ -757,7 +757,8 @@ int fdtbx_batch_profile_stacked(const fdtbx_batch_entry* entries, int32_t n_mode
  *              unit_pairs) units per item, n_units in all
  *   unit_item  device int32 [n_units]: the item of each unit
  *   partials   device float32 [n_units][128] scratch
- * Does not allocate, copy to the host or synchronise. */
+ * Where every list is empty there is no unit (n_units 0): unit_item, sidx and partials may then
+ * be NULL, and the images are zero.  Does not allocate, copy to the host or synchronise. */
 int fdtbx_batch_profile_units(const fdtbx_batch_entry* entries, int32_t n_models, const int64_t* stack_off,
                               const int64_t* stack_items, int64_t n_items, const int64_t* unit_ptr,
                               const int32_t* unit_item, int64_t n_units, int64_t unit_pairs, const float* refl,

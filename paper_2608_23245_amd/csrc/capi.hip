@@ -555,8 +555,8 @@ extern "C" int fdtbx_batch_profile_units(const fdtbx_batch_entry* entries, int32
                                          float* partials, void* stream) {
   if (!entries || n_models <= 0 || n_items < 0 || n_units < 0 || unit_pairs < 1)
     return fail(FDTBX_ERR_INVALID_ARGUMENT, "bad sizes");
-  if (!stack_off || !stack_items || !unit_ptr || !unit_item || !refl || !nodes || !pix || !tile || !stile || !srowptr ||
-      !sidx || !image || !partials)
+  if (!stack_off || !stack_items || !unit_ptr || !refl || !nodes || !pix || !tile || !stile || !srowptr || !image ||
+      (n_units > 0 && (!unit_item || !sidx || !partials)))
     return fail(FDTBX_ERR_INVALID_ARGUMENT, "null pointer");
   if (n_items > INT32_MAX || n_units > INT32_MAX) return fail(FDTBX_ERR_UNSUPPORTED, "more than 2^31 items or units");
   return launch_batch_profile_units(entries, stack_off, stack_items, n_items, unit_ptr, unit_item, n_units, unit_pairs,

@@ -14,7 +14,8 @@ torch = pytest.importorskip("torch")
 if not torch.cuda.is_available():
     pytest.skip("no GPU", allow_module_level=True)
 
-from paper_2608_23245_amd.batch import BatchEngine  # noqa: E402
+from paper_2608_23245_amd import binding as B  # noqa: E402
+from paper_2608_23245_amd.batch import BatchEngine, GraphStep  # noqa: E402
 
 
 def unreached(seed, **geom):
@@ -33,7 +34,7 @@ def step(wls, **kw):
 
 
 @pytest.mark.parametrize("deterministic", [False, True])
-@pytest.mark.parametrize("stacked", [False])
+@pytest.mark.parametrize("stacked", [True, False])
 @pytest.mark.parametrize("n", [1, 3])
 def test_no_list_holds_a_pair(n, stacked, deterministic):
     be, img, grads, glob = step([unreached(70 + i, tile_w=(0, 16)[i % 2]) for i in range(n)], stacked=stacked,
@@ -46,7 +47,7 @@ def test_no_list_holds_a_pair(n, stacked, deterministic):
         assert torch.count_nonzero(v).item() == 0, k
 
 
-@pytest.mark.parametrize("stacked", [False])
+@pytest.mark.parametrize("stacked", [True, False])
 def test_beside_a_model_that_is_reached(stacked):
     full = W.small(75)
     _, img1, g1, glob1 = step([full], stacked=stacked, deterministic=True)
@@ -58,3 +59,36 @@ def test_beside_a_model_that_is_reached(stacked):
     assert torch.equal(glob[1], glob1[0]) and torch.count_nonzero(glob[[0, 2]]).item() == 0
     for k in g:
         assert torch.equal(g[k][be.atom_off[1]:be.atom_off[2]], g1[k]), k
+
+
+def test_empty_batch_in_a_graph():
+    be = BatchEngine([unreached(78)])
+    gs = GraphStep(be, torch.full_like(be.image, 0.5))
+    gs.capture()
+    for _ in range(3):
+        be.image.fill_(-1.0)
+        be.d_globals.fill_(-1.0)
+        gs.replay()
+        torch.cuda.synchronize()
+        assert torch.count_nonzero(be.image).item() == 0 and torch.count_nonzero(be.d_globals).item() == 0
+
+
+def test_units_entry_without_units():
+    """No unit: neither a unit table nor its sums nor a list are needed, and the items' pixels
+    are written as zeros; with units their pointers are required."""
+    be = BatchEngine([unreached(79)])
+    be.image.fill_(-1.0)
+    p = B._ptr
+
+    def call(n_units):
+        return B.lib().fdtbx_batch_profile_units(
+            p(be.entries), be.n, p(be.stack_off), p(be.stack_items), int(be.stack_items.shape[0]), p(be.unit_ptr), None, n_units,
+            be.unit_pairs, p(be.refl), p(be.nodes), p(be.pix), p(be.tile), p(be.stile), p(be.srowptr), None, p(be.image), None,
+            B._stream())
+
+    assert call(1) == -1  # FDTBX_ERR_INVALID_ARGUMENT, before any launch
+    torch.cuda.synchronize()
+    assert bool((be.image == -1.0).all())
+    assert call(0) == 0
+    torch.cuda.synchronize()
+    assert torch.count_nonzero(be.image).item() == 0
