@@ -45,6 +45,15 @@ inline int32_t lcols_of(const fdtbx_geometry* g) { return (g->mirror & 1) ? (til
 inline int32_t lrows_of(const fdtbx_geometry* g) { return (g->mirror & 2) ? (tiles_y_of(g) + 1) / 2 : tiles_y_of(g); }
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// The grid of a launch of n > 0 workgroups, whose indices (launch_index) pass n - 1 in its last row.
+// HIP counts the threads along x in 32 bits: 2^32 of them are refused, of more only the excess runs,
+// without an error.  2^21 workgroups of up to 1024 threads stay below.
+inline dim3 launch_grid(int64_t n) {
+  const int64_t x = n < (int64_t{1} << 21) ? n : int64_t{1} << 21;
+  return dim3((unsigned)x, (unsigned)ceil_div(n, x));
+}
+__device__ inline int64_t launch_index() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 // Groups of threads that share the terms of a thread's sum in the batched structure factors and
 // their adjoint, for n blocks of 256 sums each: a batch of a few small models has tens of blocks,
 // far fewer than the card holds, and each thread's chain of terms is its time.

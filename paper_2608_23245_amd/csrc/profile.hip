@@ -448,14 +448,15 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_
 // wave per item the longest list took 120 ms, nearly half of a forward of 32 models.
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_b_profile_units(
     const fdtbx_batch_entry* __restrict__ ent, const int64_t* __restrict__ soff, const int64_t* __restrict__ items,
-    const int64_t* __restrict__ unit_ptr, const int32_t* __restrict__ unit_item, int64_t U,
+    const int64_t* __restrict__ unit_ptr, const int32_t* __restrict__ unit_item, int64_t n_units, int64_t U,
     const float* __restrict__ refl, const float* __restrict__ nodes, const double* __restrict__ pix,
     const double* __restrict__ tile, const double* __restrict__ stile, const int64_t* __restrict__ srowptr,
     const int32_t* __restrict__ sidx, float* __restrict__ image, float* __restrict__ partials) {
   __shared__ float4 qn[128];
   __shared__ int bq[64];
   __shared__ int qk[128];  // node indices of the queue (the Hosemann support edge)
-  const int64_t u = blockIdx.x;
+  const int64_t u = launch_index();
+  if (u >= n_units) return;
   const int k = unit_item[u];
   StackedItem it;
   stacked_item(ent, soff, items[k], refl, nodes, pix, tile, stile, srowptr, sidx, image, it);
@@ -469,10 +470,11 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_
 
 __global__ void __launch_bounds__(64) k_b_unit_reduce(
     const fdtbx_batch_entry* __restrict__ ent, const int64_t* __restrict__ soff, const int64_t* __restrict__ items,
-    const int64_t* __restrict__ unit_ptr, const double* __restrict__ pix, const double* __restrict__ tile,
+    int64_t n_items, const int64_t* __restrict__ unit_ptr, const double* __restrict__ pix, const double* __restrict__ tile,
     const double* __restrict__ stile, const int64_t* __restrict__ srowptr, float* __restrict__ image,
     const float* __restrict__ partials) {
-  const int64_t k = blockIdx.x;
+  const int64_t k = launch_index();
+  if (k >= n_items) return;
   StackedItem it;
   stacked_item(ent, soff, items[k], nullptr, nullptr, pix, tile, stile, srowptr, nullptr, image, it);
   float sa = 0.0f, sb = 0.0f;
@@ -492,12 +494,12 @@ int launch_batch_profile_units(const fdtbx_batch_entry* ent, const int64_t* soff
                                const double* tile, const double* stile, const int64_t* srowptr, const int32_t* sidx,
                                float* image, float* partials, hipStream_t s) {
   if (n_units > 0) {
-    hipLaunchKernelGGL(k_b_profile_units, dim3((unsigned)n_units), dim3(64), 0, s, ent, soff, items, unit_ptr, unit_item,
-                       unit_pairs, refl, nodes, pix, tile, stile, srowptr, sidx, image, partials);
+    hipLaunchKernelGGL(k_b_profile_units, launch_grid(n_units), dim3(64), 0, s, ent, soff, items, unit_ptr, unit_item,
+                       n_units, unit_pairs, refl, nodes, pix, tile, stile, srowptr, sidx, image, partials);
     FDTBX_LAUNCH_CHECK("batch profile units");
   }
   if (n_items > 0) {
-    hipLaunchKernelGGL(k_b_unit_reduce, dim3((unsigned)n_items), dim3(64), 0, s, ent, soff, items, unit_ptr, pix, tile,
+    hipLaunchKernelGGL(k_b_unit_reduce, launch_grid(n_items), dim3(64), 0, s, ent, soff, items, n_items, unit_ptr, pix, tile,
                        stile, srowptr, image, (const float*)partials);
     FDTBX_LAUNCH_CHECK("batch profile unit sums");
   }
