@@ -165,7 +165,7 @@ __global__ void __launch_bounds__(256) k_unit_weight(ProfParams q, UnitTable T, 
                                                      int64_t n_tiles, const float* __restrict__ refl,
                                                      const float* __restrict__ nodes, const double* __restrict__ tile,
                                                      const int32_t* __restrict__ idx) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t i = launch_index() * 256 + threadIdx.x;
   if (i < kQueues) T.ctr[i * kQueueStride] = 0;
   const int64_t p = i >> 6;
   const int lane = threadIdx.x & 63;
@@ -234,7 +234,7 @@ __global__ void __launch_bounds__(256) k_unit_fill(ProfParams q, UnitTable T, co
                                                    int64_t n_tiles, const float* __restrict__ refl,
                                                    const float* __restrict__ nodes, const double* __restrict__ tile,
                                                    const int32_t* __restrict__ idx) {
-  const int64_t p = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
+  const int64_t p = (launch_index() * 256 + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
   if (p >= kXcds * T.nj) return;
   const int64_t b = (p % T.nj) * kXcds + p / T.nj;
@@ -312,7 +312,7 @@ __global__ void __launch_bounds__(256) k_unit_reduce(ProfParams q, UnitTable T, 
                                                      const double* __restrict__ tile, const float* __restrict__ partials,
                                                      float* __restrict__ image) {
   __shared__ float sum[3][64];
-  const int64_t b = blockIdx.x;
+  const int64_t b = launch_index();
   const int t = slot_tile(q, T, b);
   if (t < 0) return;  // uniform
   const int lane = (int)threadIdx.x & 63, wv = (int)threadIdx.x >> 6;
@@ -558,12 +558,12 @@ int launch_balanced(const fdtbx_model* model, const float* refl, const float* no
   T.weigh_most = min64(weigh_most(q, model->geom.unit_pairs), pair_cap);  // more pairs than idx holds are not read
   float* partials = (float*)((char*)ws + L.partials);
   const int64_t n_tiles = (int64_t)q.tiles_x * q.tiles_y;
-  const unsigned gp = (unsigned)ceil_div(kXcds * L.nj, 4);
-  hipLaunchKernelGGL(k_unit_weight, dim3(gp), dim3(256), 0, s, q, T, offsets, n_tiles, refl, nodes, tile, idx);
+  const dim3 gp = launch_grid(ceil_div(kXcds * L.nj, 4));
+  hipLaunchKernelGGL(k_unit_weight, gp, dim3(256), 0, s, q, T, offsets, n_tiles, refl, nodes, tile, idx);
   FDTBX_LAUNCH_CHECK("balanced profile: unit weights");
   hipLaunchKernelGGL(k_unit_scan, dim3(1), dim3(1024), 0, s, T, offsets, n_tiles);
   FDTBX_LAUNCH_CHECK("balanced profile: unit scan");
-  hipLaunchKernelGGL(k_unit_fill, dim3(gp), dim3(256), 0, s, q, T, offsets, n_tiles, refl, nodes, tile, idx);
+  hipLaunchKernelGGL(k_unit_fill, gp, dim3(256), 0, s, q, T, offsets, n_tiles, refl, nodes, tile, idx);
   FDTBX_LAUNCH_CHECK("balanced profile: unit fill");
   auto launch = [&](auto units) { return units(q, refl, nodes, pix, tile, offsets, idx, T, partials, s); };
   const bool split = q.n >= kSplitNodes;
@@ -575,7 +575,7 @@ int launch_balanced(const fdtbx_model* model, const float* refl, const float* no
   else
     rc = split ? launch(launch_units<FDTBX_LINESHAPE_LAUE, true>) : launch(launch_units<FDTBX_LINESHAPE_LAUE, false>);
   if (rc) return rc;
-  hipLaunchKernelGGL(k_unit_reduce, dim3((unsigned)L.n_slots), dim3(256), 0, s, q, T, pix, tile, (const float*)partials,
+  hipLaunchKernelGGL(k_unit_reduce, launch_grid(L.n_slots), dim3(256), 0, s, q, T, pix, tile, (const float*)partials,
                      image);
   FDTBX_LAUNCH_CHECK("balanced profile: reduce");
   return FDTBX_OK;
