@@ -181,7 +181,7 @@ __global__ void __launch_bounds__(256) k_pair_reduce(int64_t n, const int64_t* _
                                                      const int32_t* __restrict__ refl_pairs,
                                                      const float* __restrict__ partials, const int64_t* __restrict__ mate,
                                                      int32_t updown, double* __restrict__ sums) {
-  const int64_t r = (int64_t)blockIdx.x * (256 / kReduceLanes) + threadIdx.x / kReduceLanes;
+  const int64_t r = launch_index() * (256 / kReduceLanes) + threadIdx.x / kReduceLanes;
   const int l = threadIdx.x % kReduceLanes;
   double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   if (r < n) {
@@ -200,7 +200,7 @@ __global__ void __launch_bounds__(256) k_pair_reduce(int64_t n, const int64_t* _
 
 int launch_pair_reduce(int64_t n, const int64_t* refl_ptr, const int32_t* refl_pairs, const float* partials,
                        const int64_t* mate, int32_t updown, double* sums, hipStream_t s) {
-  hipLaunchKernelGGL(k_pair_reduce, dim3((unsigned)ceil_div(n * kReduceLanes, 256)), dim3(256), 0, s, n, refl_ptr,
+  hipLaunchKernelGGL(k_pair_reduce, launch_grid(ceil_div(n * kReduceLanes, 256)), dim3(256), 0, s, n, refl_ptr,
                      refl_pairs, partials, mate, updown, sums);
   FDTBX_LAUNCH_CHECK("pair reduction");
   return FDTBX_OK;

@@ -4,7 +4,8 @@ dimension and of more runs the excess alone, without an error.
 The balanced pattern launch of a detector of 2^24 tiles and more (its unit sums take four waves
 a tile): short lists in tiles spread over it and in its last ones, against the per-tile launch over
 the same lists (float32 rounding of the same sums, 1e-5 of relative L2) and exactly zero in every
-tile without a list."""
+tile without a list.  The pair reduction of 2^28 reflections and more (sixteen lanes each): rows
+spread over the list and in its last places, whole numbers that any order sums exactly."""
 import ctypes
 import dataclasses
 
@@ -62,3 +63,27 @@ def test_balanced_launch_of_many_tiles(columns):
     ref = ref.view(4096, 8, columns, 8).permute(0, 2, 1, 3).reshape(n_tiles, 64)[in_list].double()
     assert ref.max() > 0
     assert ((tiles[in_list].double() - ref).norm() / ref.norm()).item() <= 1e-5
+
+
+@pytest.mark.parametrize("n", [1 << 28, (1 << 28) + 1])
+def test_pair_reduction_of_many_reflections(n):
+    rng = np.random.default_rng(n)
+    rows = torch.as_tensor(np.unique(np.concatenate([rng.integers(0, n, 200), np.arange(n - 3, n)]))).cuda()
+    length = torch.as_tensor(rng.integers(1, 40, rows.shape[0])).cuda()
+    ptr = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    ptr[rows + 1] = length
+    ptr = ptr.cumsum_(0)
+    total = int(length.sum())
+    part = torch.as_tensor(rng.integers(-99, 100, (total, 12)), dtype=torch.float32).cuda()
+    pairs = torch.as_tensor(rng.permutation(total), dtype=torch.int32).cuda()
+    print(f"{n} reflections, {total} pairs", flush=True)
+    sums = torch.full((n, 6), -1.0, dtype=torch.float64, device="cuda")
+    p = B._ptr
+    B._check(B.lib().fdtbx_pair_reduce(n, p(ptr), p(pairs), p(part), None, 0, p(sums), B._stream()))
+    torch.cuda.synchronize()
+    at = 0
+    for r, m in zip(rows.tolist(), length.tolist()):
+        assert torch.equal(sums[r], part[pairs[at:at + m].long(), :6].double().sum(0)), r
+        at += m
+    sums[rows] = 0.0
+    assert torch.count_nonzero(sums).item() == 0
