@@ -32,7 +32,6 @@ static constexpr int kMaxTypes = 16;
 // Atoms summed in float32 before they are added in binary64.  The float32 sums of a whole chunk
 // were most of the error: 1.7e-7 to 6.4e-7 of |F| for 160 to 30000 atoms, 1.0e-7 to 1.6e-7 so.
 static constexpr int kSFGroup = 8;
-static_assert(kSFThreads % kSFGroup == 0, "a partly filled group of atoms ends inside the LDS array");
 static constexpr int64_t kSFBlocks = 2048;  // two rounds of the chip's 256 compute units at four blocks each
 
 struct SFParams {
@@ -57,11 +56,6 @@ struct AtomsLds {
     xy[i] = make_double2((double)x[j], (double)y[j]);
     zb[i] = {(double)z[j], -B[j] * 1.4426950408889634f, o[j]};
     type[i] = t * row;
-  }
-  __device__ __forceinline__ void put_none(int i) {  // adds nothing
-    xy[i] = make_double2(0.0, 0.0);
-    zb[i] = {0.0, 0.0f, 0.0f};
-    type[i] = 0;
   }
 };
 
@@ -122,27 +116,32 @@ __global__ void __launch_bounds__(kSFThreads) k_sf_partial(SFParams p, const flo
     }
     for (int64_t g0 = a0; g0 < a1; g0 += kSFThreads) {
       __syncthreads();
-      if (g0 + threadIdx.x < a1)
-        at.put(threadIdx.x, x, y, z, B, occ, type, g0 + threadIdx.x, p.n_types, kSFThreads * K);
-      else
-        at.put_none(threadIdx.x);
+      if (g0 + threadIdx.x < a1) at.put(threadIdx.x, x, y, z, B, occ, type, g0 + threadIdx.x, p.n_types, kSFThreads * K);
       __syncthreads();
       const int cnt = (int)((a1 - g0) < kSFThreads ? (a1 - g0) : kSFThreads);
       if (any) {
-        for (int i0 = 0; i0 < cnt; i0 += kSFGroup) {
-          float gr[K] = {}, gi[K] = {};
-#pragma unroll 4
-          for (int i = i0; i < i0 + kSFGroup; ++i) {
-            const double2 xy = at.xy[i];
-            const auto zb = at.zb[i];
-            const float* f = ftab + at.type[i] + threadIdx.x * K;
+        float gr[K], gi[K];
+        auto term = [&](int i) {
+          const double2 xy = at.xy[i];
+          const auto zb = at.zb[i];
+          const float* f = ftab + at.type[i] + threadIdx.x * K;
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-              const float fr = sf_phase(h[k], kk[k], l[k], xy, zb.z);
-              const float amp = zb.occ * f[k] * __builtin_amdgcn_exp2f(zb.nBl2e * s2[k]);
-              gr[k] = fmaf(amp, __builtin_amdgcn_cosf(fr), gr[k]);
-              gi[k] = fmaf(amp, __builtin_amdgcn_sinf(fr), gi[k]);
-            }
+          for (int k = 0; k < K; ++k) {
+            const float fr = sf_phase(h[k], kk[k], l[k], xy, zb.z);
+            const float amp = zb.occ * f[k] * __builtin_amdgcn_exp2f(zb.nBl2e * s2[k]);
+            gr[k] = fmaf(amp, __builtin_amdgcn_cosf(fr), gr[k]);
+            gi[k] = fmaf(amp, __builtin_amdgcn_sinf(fr), gi[k]);
+          }
+        };
+        for (int i0 = 0; i0 < cnt; i0 += kSFGroup) {
+#pragma unroll
+          for (int k = 0; k < K; ++k) gr[k] = gi[k] = 0.0f;
+          if (i0 + kSFGroup <= cnt) {  // uniform
+#pragma unroll 4
+            for (int i = i0; i < i0 + kSFGroup; ++i) term(i);
+          } else {
+#pragma unroll 1
+            for (int i = i0; i < cnt; ++i) term(i);
           }
 #pragma unroll
           for (int k = 0; k < K; ++k) {
