@@ -11,7 +11,8 @@
 //
 // F(-h) = conj F(h): an enumerated list is symmetric, reflection n - 1 - i being the Friedel
 // mate of reflection i, so a block of the first half writes the second half's sums too after it
-// has compared the indices; where a block's mates are not mates, it evaluates them as well.
+// has compared the indices; where a block's mates are not mates, it evaluates them as well, or
+// where the launch is short a second block does (blockIdx.z).
 //
 // Bound: the vector instructions of a term, 6 binary64 ones of 5 cycles per wave and SIMD, 3
 // transcendentals of 8.4 and 7 float32 ones of 2.6, or 73 cycles; 73 are reached.  The inner
@@ -32,7 +33,13 @@ static constexpr int kMaxTypes = 16;
 // Atoms summed in float32 before they are added in binary64.  The float32 sums of a whole chunk
 // were most of the error: 1.7e-7 to 6.4e-7 of |F| for 160 to 30000 atoms, 1.0e-7 to 1.6e-7 so.
 static constexpr int kSFGroup = 8;
-static constexpr int64_t kSFBlocks = 2048;  // two rounds of the chip's 256 compute units at four blocks each
+static constexpr int64_t kSFBlocks = 2048;  // eight blocks on each of the chip's 256 compute units
+// Up to here the blocks of both halves fit on the chip together, and the second half has blocks of
+// its own, which end at once where the mates are mates.  One after the other / side by side, the
+// mates no mates: 1000 reflections of 5000 atoms 21.1 / 18.4 us (with mates 18.0 / 17.8), 10000 of
+// 1000 21.4 / 17.8, 5000 of 5000 36.0 / 31.9; with 2051 blocks the ended ones cost more than they
+// gain (150000 of 5000, with mates: 214 / 224).
+static constexpr int64_t kSFBothHalves = kSFBlocks / 2;
 
 struct SFParams {
   double as[9];          // reciprocal basis rows a*, b*, c*
@@ -94,7 +101,7 @@ __global__ void __launch_bounds__(kSFThreads) k_sf_partial(SFParams p, const flo
   mates = __syncthreads_and(mates);
   const int64_t a0 = (int64_t)blockIdx.y * p.chunk;
   const int64_t a1 = a0 + p.chunk < p.n_atoms ? a0 + p.chunk : p.n_atoms;
-  for (int second = 0; second < (mates ? 1 : 2); ++second) {  // uniform
+  for (int second = (int)blockIdx.z; second < (mates ? 1 : 2); second += (int)gridDim.z) {  // uniform
     double h[K], kk[K], l[K];
     float s2[K];
     double re[K], im[K];
@@ -133,21 +140,29 @@ __global__ void __launch_bounds__(kSFThreads) k_sf_partial(SFParams p, const flo
             gi[k] = fmaf(amp, __builtin_amdgcn_sinf(fr), gi[k]);
           }
         };
-        for (int i0 = 0; i0 < cnt; i0 += kSFGroup) {
+        auto clear = [&] {
 #pragma unroll
           for (int k = 0; k < K; ++k) gr[k] = gi[k] = 0.0f;
-          if (i0 + kSFGroup <= cnt) {  // uniform
-#pragma unroll 4
-            for (int i = i0; i < i0 + kSFGroup; ++i) term(i);
-          } else {
-#pragma unroll 1
-            for (int i = i0; i < cnt; ++i) term(i);
-          }
+        };
+        auto add = [&] {
 #pragma unroll
           for (int k = 0; k < K; ++k) {
             re[k] += (double)gr[k];
             im[k] += (double)gi[k];
           }
+        };
+        const int full = cnt / kSFGroup * kSFGroup;
+        for (int i0 = 0; i0 < full; i0 += kSFGroup) {
+          clear();
+#pragma unroll 4
+          for (int i = i0; i < i0 + kSFGroup; ++i) term(i);
+          add();
+        }
+        if (full < cnt) {
+          clear();
+#pragma unroll 1
+          for (int i = full; i < cnt; ++i) term(i);
+          add();
         }
       }
     }
@@ -162,11 +177,14 @@ __global__ void __launch_bounds__(kSFThreads) k_sf_partial(SFParams p, const flo
   }
 }
 
+// The chunks' sums, added in order, eight loads in flight (one at a time waited 0.25 us for each:
+// 50 reflections of 50000 atoms, 782 chunks, 205 us with the sums before it, 46 so).
 __global__ void k_sf_final(int64_t n_hkl, int32_t n_chunks, const float2* __restrict__ part, float* __restrict__ F,
                            float* __restrict__ F2) {
   int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= n_hkl) return;
   double re = 0.0, im = 0.0;
+#pragma unroll 8
   for (int c = 0; c < n_chunks; ++c) {
     float2 v = part[(int64_t)c * n_hkl + r];
     re += v.x;
@@ -288,7 +306,12 @@ static int sf_split(int64_t n_hkl, int64_t n_atoms, int32_t* n_chunks, int64_t* 
   const int64_t half = (n_hkl + 1) / 2, maxc = ceil_div(n_atoms, 64);
   const int k = ceil_div(half, 2 * kSFThreads) * ceil_div(n_atoms, 1024) >= kSFBlocks ? 2 : 1;
   const int64_t nb = ceil_div(half, k * kSFThreads);
-  int64_t nc = ceil_div(kSFBlocks, nb);  // fill the chip
+  // fill the chip: with one reflection per thread eight blocks of a compute unit run at once, and the
+  // 2051 blocks that ceil makes of 293 leave it a ninth: 150000 reflections of 5000 atoms 0.214 ms,
+  // 0.202 with the 1758 of floor, and 0.420 / 0.395 where no mates are mates.  From 410 blocks floor
+  // leaves too few (489 blocks: 0.171 / 0.172), and so it does with two per thread, whose blocks are
+  // fewer and longer (290000 of 50000 3.34 / 3.41).
+  int64_t nc = k == 1 && nb <= kSFBlocks / 5 ? kSFBlocks / nb : ceil_div(kSFBlocks, nb);
   if (nc > maxc) nc = maxc;
   if (nc < 1) nc = 1;
   *chunk = ceil_div(n_atoms, nc);
@@ -357,7 +380,8 @@ extern "C" int fdtbx_structure_factors(const fdtbx_cell* cell, int64_t n_atoms, 
   const int per_thread = sf_split(n_hkl, n_atoms, &p.n_chunks, &p.chunk);
   hipStream_t s = (hipStream_t)stream;
   float2* part = (float2*)ws;
-  const dim3 grid((unsigned)ceil_div((n_hkl + 1) / 2, per_thread * kSFThreads), (unsigned)p.n_chunks);
+  const unsigned nb = (unsigned)ceil_div((n_hkl + 1) / 2, per_thread * kSFThreads);
+  const dim3 grid(nb, (unsigned)p.n_chunks, (int64_t)nb * p.n_chunks <= kSFBothHalves ? 2 : 1);
   const size_t lds = (size_t)n_types * kSFThreads * per_thread * sizeof(float);
   if (per_thread == 2)
     hipLaunchKernelGGL(k_sf_partial<2>, grid, dim3(kSFThreads), lds, s, p, x, y, z, B, occ, type, ff, hkl, part);
