@@ -22,6 +22,7 @@
 #include "internal.h"
 #include "profile_common.h"
 #include "profile_tile.h"
+#include "ranges.h"
 
 namespace fdtbx {
 
@@ -286,7 +287,7 @@ __global__ void __launch_bounds__(64 * WAVES, cyl_occupancy(LS)) k_cyl(CylParams
       }
       // a coordinate of the ring is a sinusoid of the azimuth: over an arc of half-angle d it stays
       // within its amplitude times 1 - cos d of its values at the arc's ends
-      const bool reach = jb <= jh && jb + kJB > jl;
+      const bool reach = ring_block_meets(jl, jh, jb, kJB);
       float lo[3], hi[3], pl[3], ph[3];
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
