@@ -7,6 +7,7 @@
 #include <math.h>
 
 #include "internal.h"
+#include "ranges.h"
 
 namespace fdtbx {
 
@@ -165,10 +166,8 @@ __device__ __forceinline__ void load_pair(const float* __restrict__ rec, PairRec
 // Node index range that query points p with p.S in [sl, sh], p.e1 in [l1, h1] and
 // p.e2 in [l2, h2] can reach.  A node in the support of p satisfies |s.v - p.v| <= rho_v
 // for v in {S, e1, e2} (rho_v: support extents); s.S = r0 c is in [r0 cmin, r0];
-// d_j = (s.e_j)/(s.S).  An eighth of a node of margin on each side absorbs the float32 rounding
-// of these bounds, hardware reciprocals included: d_j and its place on the grid carry a few
-// parts in 10^7 of |d_j| <= 2 T, which is n times that in nodes (1e-4 at n = 256), and p.v the
-// same part of |p|, for which rho_v is widened as well.  A whole node, as it was, made the window
+// d_j = (s.e_j)/(s.S).  window_margin on each side absorbs the float32 rounding of these bounds, for
+// which rho_v is widened as well.  A whole node, as it was, made the window
 // of a coarse grid, a few nodes wide, about half as large again, and its scan is what a pair
 // with few nodes costs: 0.377 -> 0.350 ms for 20 Hosemann nodes per side at 6 entries a pair,
 // 0.565 -> 0.545 ms for a draft of 24 Laue nodes.
@@ -187,8 +186,9 @@ __device__ static inline bool node_window_ranges(const ProfParams& q, float r0, 
   bounds(l1 - r1, h1 + r1, &d1l, &d1h);
   bounds(l2 - r2, h2 + r2, &d2l, &d2h);
   // node i sits at d = -T + (i + 1/2) h
-  auto lo_idx = [&](float d) { return (int)ceilf((d + q.T) * q.inv_h - (0.5f + 0.125f)); };
-  auto hi_idx = [&](float d) { return (int)floorf((d + q.T) * q.inv_h - (0.5f - 0.125f)); };
+  const float margin = window_margin(q.inv_h);
+  auto lo_idx = [&](float d) { return (int)ceilf((d + q.T) * q.inv_h - (0.5f + margin)); };
+  auto hi_idx = [&](float d) { return (int)floorf((d + q.T) * q.inv_h - (0.5f - margin)); };
   float big = 2.0f * q.T;
   d1l = fmaxf(d1l, -big);
   d2l = fmaxf(d2l, -big);
