@@ -242,12 +242,14 @@ __global__ void __launch_bounds__(256) k_list_reduce(int64_t n, int64_t n_tiles,
     for (int c = 0; c < 6; ++c) sums[6 * r + c] = v[c];
 }
 
-// The searches cost about as much as sorting the pairs where there are 2^25 of them.  Backward
-// pass in ms with the sort / with the searches: 436 reflections in 255 tiles 0.29 / 0.16; 49962
-// reflections in 16 tiles 1.31 / 0.58, in 256 tiles (2^23.6) 1.82 / 1.22, in 1024 tiles (2^25.6)
-// 4.83 / 4.90.  The sort takes the capacity of the lists through 20 launches, at least 2^20 pairs
-// as a plan makes it.
-constexpr int64_t kListReduceMost = int64_t{1} << 25;
+// The sort takes the capacity of the lists through 20 launches, the searches n_hkl * n_tiles look-ups
+// whatever the lists hold.  Backward pass in us with the sort / with the searches, 8 nodes per side:
+// 49962 reflections in 4 tiles (2^17.6 look-ups) 327 / 230, in 64 (2^21.6) 416 / 345, in 144 (2^22.8) 512 /
+// 528, in 256 (2^23.6) 554 / 859, in 576 (2^24.8) 859 / 1702; 6182 reflections in 1024 tiles (2^22.6) 352
+// / 292, in 4096 (2^24.6) 480 / 734; 1840 in 4096 (2^22.8) 249 / 185 with a capacity of 2^20 pairs, 176 /
+// 183 with that of its lists.  The capacity has no part in the rule: the two routes add in different
+// orders, and a plan that grew must give the bits of one that did not.
+constexpr int64_t kListReduceMost = int64_t{1} << 23;
 
 bool list_reduce_pays(int64_t n_hkl, int64_t n_tiles) { return n_hkl <= kListReduceMost / n_tiles; }
 
