@@ -715,7 +715,7 @@ int launch_batch_backward(const fdtbx_batch_entry* ent, int32_t n_models, const 
                           const double* pix, const double* tile, const int64_t* rowptr, const int32_t* idx, const float* F,
                           const float* refl, const float* nodes, const float* grad_image, double* sums, double* part,
                           float* dF2, float* d_x, float* d_y, float* d_z, float* d_B, float* d_occ, double* d_globals,
-                          int64_t* counter, const PairOrder* fixed, hipStream_t s) {
+                          const PairOrder* fixed, hipStream_t s) {
   if (fixed) {
     const int rc = fill(fixed->partials, 12 * fixed->n_pairs, 0.0f, s);
     if (rc) return rc;

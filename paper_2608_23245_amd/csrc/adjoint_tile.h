@@ -293,7 +293,7 @@ __device__ __forceinline__ void adjoint_range(const ProfParams& q, const float* 
   }
 }
 
-template <int LS, int WAVES = 1, bool PRE = false>
+template <int LS, int WAVES>
 __device__ __forceinline__ void adjoint_tile(const ProfParams& q, const float* __restrict__ refl, const float* __restrict__ nodes,
                                              const double* __restrict__ pix, const double* __restrict__ tile,
                                              const int64_t* __restrict__ offsets, const int32_t* __restrict__ idx,
@@ -301,7 +301,7 @@ __device__ __forceinline__ void adjoint_tile(const ProfParams& q, const float* _
                                              float* __restrict__ partials, const int t, float4* qn, float2* qd, int* bq,
                                              float* gw, int* qk = nullptr) {
   const int wv = WAVES > 1 ? (int)(threadIdx.x >> 6) : 0;
-  adjoint_range<LS, PRE>(q, refl, nodes, pix, tile, idx, grad_image, n_hkl, sums, partials, t, offsets[t] + 64 * wv,
+  adjoint_range<LS>(q, refl, nodes, pix, tile, idx, grad_image, n_hkl, sums, partials, t, offsets[t] + 64 * wv,
                     offsets[t + 1], 64 * WAVES, 64, qn + 128 * wv, qd + 128 * wv, bq + 64 * wv, gw + 128 * wv,
                     qk ? qk + 128 * wv : nullptr);
 }

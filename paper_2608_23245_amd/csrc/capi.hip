@@ -591,7 +591,7 @@ extern "C" int fdtbx_batch_backward(const fdtbx_batch_entry* entries, int32_t n_
     return fail(FDTBX_ERR_INVALID_ARGUMENT, "null pointer");
   return launch_batch_backward(entries, n_models, refl_blocks, n_rb, model_rb, atom_blocks, n_ab, tile_items, n_items,
                                n_hkl_total, hkl, x, y, z, B, occ, type, ff, pix, tile, rowptr, idx, F, refl, nodes, grad_image,
-                               sums, part, dF2, d_x, d_y, d_z, d_B, d_occ, d_globals, counter, nullptr, (hipStream_t)stream);
+                               sums, part, dF2, d_x, d_y, d_z, d_B, d_occ, d_globals, nullptr, (hipStream_t)stream);
 }
 
 extern "C" int fdtbx_batch_backward_deterministic(
@@ -612,7 +612,7 @@ extern "C" int fdtbx_batch_backward_deterministic(
   const PairOrder fixed = {partials, n_pairs_total, refl_ptr, refl_pairs, mate};
   return launch_batch_backward(entries, n_models, refl_blocks, n_rb, model_rb, atom_blocks, n_ab, tile_items, n_items,
                                n_hkl_total, hkl, x, y, z, B, occ, type, ff, pix, tile, rowptr, idx, F, refl, nodes, grad_image,
-                               sums, part, dF2, d_x, d_y, d_z, d_B, d_occ, d_globals, counter, &fixed, (hipStream_t)stream);
+                               sums, part, dF2, d_x, d_y, d_z, d_B, d_occ, d_globals, &fixed, (hipStream_t)stream);
 }
 
 extern "C" size_t fdtbx_batch_entry_size(void) { return sizeof(fdtbx_batch_entry); }

@@ -294,7 +294,7 @@ int launch_batch_backward(const fdtbx_batch_entry* ent, int32_t n_models, const 
                           const double* pix, const double* tile, const int64_t* rowptr, const int32_t* idx, const float* F,
                           const float* refl, const float* nodes, const float* grad_image, double* sums, double* part,
                           float* dF2, float* d_x, float* d_y, float* d_z, float* d_B, float* d_occ, double* d_globals,
-                          int64_t* counter, const PairOrder* fixed, hipStream_t s);
+                          const PairOrder* fixed, hipStream_t s);
 
 // Cell frame in the laboratory convention: rows of avec are a, b, c; rows of
 // astar are a*, b*, c*.  Binary64, operation order fixed (compiled without
