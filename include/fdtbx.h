@@ -81,9 +81,11 @@ typedef struct fdtbx_geometry {
                                  compute unit), else 2.  The batched kernels ignore it */
   int32_t unit_pairs;         /* pairs per work unit of fdtbx_profile_balanced (and so of
                                  fdtbx_profile_pattern): 0 is the library's choice from the pair
-                                 count (fdtbx_unit_pairs); the image depends on it in the last bits
-                                 (the grouping of the sums), so two launches that must agree bit for
-                                 bit (a folded and an unfolded one) fix it to the same value */
+                                 count (fdtbx_unit_pairs, and over a range of counts the pairs'
+                                 weights; see fdtbx_profile_balanced); the image depends on it in
+                                 the last bits (the grouping of the sums), so two launches that must
+                                 agree bit for bit (a folded and an unfolded one) fix it to the same
+                                 nonzero value */
   double det_tilt;            /* detector tilt, radians, |det_tilt| < pi/2: the detector plane
                                  turned about its horizontal axis (through the beam centre) so that
                                  its top leans toward the sample for det_tilt > 0; pixel (y, z) then
@@ -365,12 +367,13 @@ int fdtbx_profile(const fdtbx_model* model, const float* refl, const float* node
  * lorentz) from a launch balanced over the compute units.  The launched tiles' lists are cut
  * into work units of geom.unit_pairs pairs; 0: of fdtbx_unit_pairs(n_pairs) pairs (read on the
  * device from offsets[n_tiles]), or from 8193 to 2048 n_nodes^2 pairs, of as many pairs of mean
- * weight, a pair's weight being an estimate of its time from its node window.  Persistent waves take the
- * units from queues, eight for each XCD (slot b of the launch order feeds those of XCD b % 8, in
- * slot order), each unit writes its 64 pixel sums to a slot of its own, and a second kernel adds
- * each tile's units in unit order.  So no
- * long list runs as one workgroup at the end of the launch, and the image is the same on every
- * run; it equals fdtbx_profile's to float32 rounding (the sums are grouped by unit).
+ * weight, a pair's weight being an estimate of its time from its node window (in that range a
+ * launch with 0 and one with fdtbx_unit_pairs(n_pairs) agree to float32 rounding only, outside it
+ * bit for bit).  Persistent waves take the units from queues, eight for each XCD (slot b of the
+ * launch order feeds those of XCD b % 8, in slot order), each unit writes its 64 pixel sums to a
+ * slot of its own, and a second kernel adds each tile's units in a fixed order.  So no long list
+ * runs as one workgroup at the end of the launch, and the image is the same on every run; it equals
+ * fdtbx_profile's to float32 rounding (the sums are grouped by unit).
  *   order     as for fdtbx_profile (or NULL)
  *   pair_cap  capacity of idx: offsets[n_tiles] must not exceed it (units beyond the
  *             workspace's capacity, which only a larger total would need, are not run)

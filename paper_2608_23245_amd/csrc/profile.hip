@@ -143,8 +143,9 @@ __device__ inline int pair_weight(const ProfParams& q, const float* __restrict__
 // 1.204, 7.2 million 2.36 + 4.37 / 2.65 + 4.22; at 64 nodes: 28,657 pairs 1.10 + 1.92 / 0.83 +
 // 1.42, 485,808 pairs 3.60 + 7.63 / 2.92 + 6.17, 7.2 million 22.4 + 49.1 / 21.7 + 46.4.
 // Longer lists of dense grids would still gain (28.9 million pairs 50.4 + 106 / 49.9 + 103.5, the
-// large model 1024 / 1010), but are cut by number: an unfolded launch then reproduces a folded one
-// bit for bit from the folded one's fdtbx_unit_pairs.
+// large model 1024 / 1010), but are cut by number as a fixed unit_pairs cuts them: there, and up to
+// 8192 pairs, a launch with unit_pairs 0 has the bits of one with fdtbx_unit_pairs, which callers of
+// long lists compare.  Between the two limits bit equality needs the same nonzero unit_pairs on both.
 static int64_t weigh_most(const ProfParams& q, int64_t fixed_U) {
   return fixed_U > 0 ? -1 : (int64_t)q.n * q.n * 2048;  // 2^19 pairs at 16 nodes per side, 2^23 at 64
 }
