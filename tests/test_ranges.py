@@ -12,7 +12,7 @@ CSRC = os.path.join(os.path.dirname(HERE), "paper_2608_23245_amd", "csrc")
 SOURCE = """
 #include "ranges.h"
 extern "C" int ring_block_meets(int jl, int jh, int jb, int n) { return fdtbx::ring_block_meets(jl, jh, jb, n); }
-extern "C" float window_margin(float inv_h) { return fdtbx::window_margin(inv_h); }
+extern "C" float widened_reach(float rho, float r0) { return fdtbx::widened_reach(rho, r0); }
 """
 
 
@@ -25,7 +25,7 @@ def ranges(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-ffp-contract=off", "-I", CSRC, str(src), "-o", lib],
                    check=True)
     lib = ctypes.CDLL(lib)
-    lib.window_margin.restype, lib.window_margin.argtypes = ctypes.c_float, [ctypes.c_float]
+    lib.widened_reach.restype, lib.widened_reach.argtypes = ctypes.c_float, [ctypes.c_float, ctypes.c_float]
     return lib
 
 
@@ -46,23 +46,24 @@ def f32(x):
     return np.asarray(x, dtype=np.float64).astype(F32)
 
 
-def window(n, T, axes, R, Z, r0, rho, margin):
+def window(n, T, axes, R, Z, r0, rho, widened):
     """The node window of a pixel (R, Z), in the float32 operations of pair_setup and
     node_window_ranges: axes are the (R, Z) coefficients of S, e1, e2."""
     inv_h, T32, r0 = f32(n / (2 * T)), f32(T), f32(r0)
     cmin = f32(1 / np.sqrt(1 + 2 * T * T))
     R, Z = f32(R), f32(Z)
     pS, p1, p2 = [(f32(c[0]) * R).astype(F32) + (f32(c[1]) * Z).astype(F32) for c in axes]
-    rS, r1, r2 = [(f32(r) * F32(1.0001)).astype(F32) for r in rho]
+    rS = f32(rho[0]) * F32(1.0001)
+    r1, r2 = [np.array([widened(float(a), float(b)) for a, b in zip(f32(r), r0)], dtype=F32) for r in rho[1:]]
     lo, hi = np.maximum(pS - rS, r0 * cmin * F32(0.9999)), np.minimum(pS + rS, r0 * F32(1.0001))
     inv_lo, inv_hi = (F32(1) / lo).astype(F32), (F32(1) / hi).astype(F32)
-    big, m, out = F32(2) * T32, np.array([margin(float(v)) for v in inv_h], dtype=F32), []
+    big, out = F32(2) * T32, []
     for p, r in ((p1, r1), (p2, r2)):
         dl, dh = p - r, p + r
         dl = np.maximum(dl * np.where(dl >= 0, inv_hi, inv_lo), -big)
         dh = np.minimum(dh * np.where(dh >= 0, inv_lo, inv_hi), big)
-        out.append(np.maximum(np.ceil((dl + T32) * inv_h - (F32(0.5) + m)), 0))
-        out.append(np.minimum(np.floor((dh + T32) * inv_h - (F32(0.5) - m)), n - 1))
+        out.append(np.maximum(np.ceil((dl + T32) * inv_h - F32(0.625)), 0))
+        out.append(np.minimum(np.floor((dh + T32) * inv_h - F32(0.375)), n - 1))
     assert all(v.dtype == F32 for v in (pS, rS, lo, hi, inv_lo, dl, dh))
     return lo <= hi, out
 
@@ -70,7 +71,7 @@ def window(n, T, axes, R, Z, r0, rho, margin):
 @pytest.mark.parametrize("lo,hi", [(-6, -5), (-5, -4), (-4, -3), (-3, -1.5), (-1.5, 0.3)])
 def test_window_holds_every_node_in_reach(ranges, lo, hi):
     """Pixels that lie at the very edge of a node's reach, in binary64, for grids of half extent
-    10^lo to 10^hi: the float32 window holds that node.  Supports of 10^-4 to 1 of the grid."""
+    10^lo to 10^hi: the float32 window, with its margin of an eighth of a node, holds that node.  Supports of 10^-4 to 1 of the grid."""
     rng = np.random.default_rng(int(10 * lo) + 1000)
     N = 20000
     n, T = rng.choice([16, 24, 64, 96, 256], N), 10 ** rng.uniform(lo, hi, N)
@@ -89,6 +90,6 @@ def test_window_holds_every_node_in_reach(ranges, lo, hi):
     # the reach along each axis: as far as the pixel lies from the node
     rho = [np.abs(((p - node) * e).sum(1)) * (1 + 1e-9) for e in (S, e1, e2)]
     ok, (l1, h1, l2, h2) = window(n, T, [(e[:, 0], e[:, 2]) for e in (S, e1, e2)], p[:, 0], p[:, 2], r0, rho,
-                                  ranges.window_margin)
+                                  ranges.widened_reach)
     missed = ~ok | (i1 < l1) | (i1 > h1) | (i2 < l2) | (i2 > h2)
     assert not missed.any(), f"{missed.sum()} of {N}"
