@@ -200,7 +200,7 @@ __global__ void __launch_bounds__(64 * WAVES, cyl_occupancy(LS)) k_cyl(CylParams
     const float r0 = f.at(RS_R0);
     const double rhoB = ((double)(2.0f * r0 * sqrtf(0.5f * (1.0f - q.cmin))) + (double)sqrtf(rS * rS + r1 * r1 + r2 * r2)) *
                             1.001 + 1.0e-7;
-    int jl = 1, jh = 0;  // empty
+    int jl = kNoRingFirst, jh = kNoRingLast;
     if (in) {
       const double dz = Z - ZD;
       const double num = ((R * R + RD * RD) + dz * dz) - rhoB * rhoB;
@@ -222,8 +222,7 @@ __global__ void __launch_bounds__(64 * WAVES, cyl_occupancy(LS)) k_cyl(CylParams
         }
       }
     }
-    const bool has = jl <= jh;
-    const int J0 = wave_min_i32(has ? jl : 0x7fffffff), J1 = wave_max_i32(has ? jh : -0x7fffffff);
+    const int J0 = wave_min_i32(jl), J1 = wave_max_i32(jh);
     if (J0 > J1) continue;
     HoseK hk = {};
     if (LS == FDTBX_LINESHAPE_HOSEMANN && !COUNT) hose_constants(rec, hk);

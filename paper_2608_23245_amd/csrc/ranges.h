@@ -9,10 +9,12 @@
 
 namespace fdtbx {
 
-// Whether the ring indices jb .. jb + n - 1 of a block meet a lane's jl .. jh, which is empty where
-// jl > jh: such a lane must not widen the block's node window (one off the detector has R = Z = 0,
-// which widens it to the origin).
-FDTBX_HD inline bool ring_block_meets(int jl, int jh, int jb, int n) { return jl <= jh && jb <= jh && jb + n > jl; }
+// Whether the ring indices jb .. jb + n - 1 of a block meet a lane's jl .. jh.  A lane without a ring
+// point in reach carries the range below, which meets no block (as (1, 0) does not: that one counts as
+// met by the blocks around 0): it must not widen the block's node window (a lane off the detector has
+// R = Z = 0, which widens it to the origin).
+constexpr int kNoRingFirst = 1 << 30, kNoRingLast = -(1 << 30);
+FDTBX_HD inline bool ring_block_meets(int jl, int jh, int jb, int n) { return jb <= jh && jb + n > jl; }
 
 // Half-width of a support along e1 or e2 (its extent rho about a node at radius r0), widened by the
 // float32 rounding of the query point's coordinate there: the sum of two products of rounded factors

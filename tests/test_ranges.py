@@ -12,6 +12,7 @@ CSRC = os.path.join(os.path.dirname(HERE), "paper_2608_23245_amd", "csrc")
 SOURCE = """
 #include "ranges.h"
 extern "C" int ring_block_meets(int jl, int jh, int jb, int n) { return fdtbx::ring_block_meets(jl, jh, jb, n); }
+extern "C" int no_ring(int last) { return last ? fdtbx::kNoRingLast : fdtbx::kNoRingFirst; }
 extern "C" float widened_reach(float rho, float r0) { return fdtbx::widened_reach(rho, r0); }
 """
 
@@ -30,12 +31,17 @@ def ranges(tmp_path_factory):
 
 
 def test_ring_block_meets_a_lane_that_has_points_in_it(ranges):
-    """Every small range, the empty one (1, 0) that a lane out of reach carries among them."""
+    """Every small range, and the empty one that a lane out of reach carries: it meets no block, and
+    does not move the first or last index of a wave."""
+    none = ranges.no_ring(0), ranges.no_ring(1)
+    assert none[0] > 1 << 29 and none[1] < -(1 << 29)
     for n in (1, 8):
-        for jl in range(-12, 13):
-            for jh in range(jl - 1, 13):
-                for jb in range(-24, 25):
-                    want = any(jl <= j <= jh for j in range(jb, jb + n))
+        for jb in [*range(-24, 25), 1 << 28, -(1 << 28)]:
+            assert not ranges.ring_block_meets(*none, jb, n), (jb, n)
+            for jl in range(-12, 13):
+                for jh in range(jl, 13):
+                    want = jb <= jh and jl <= jb + n - 1
+                    assert want == any(jl <= j <= jh for j in range(jb, jb + n))
                     assert bool(ranges.ring_block_meets(jl, jh, jb, n)) == want, (jl, jh, jb, n)
 
 
