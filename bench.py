@@ -280,6 +280,7 @@ def bench_medium(args):
            "waves_per_tile": waves, "pass": "forward"}
     if wl.geom.mirror and not args.no_unfolded:
         # the folded launch's pairs per work unit, so that the computed rows can be compared bit for bit
+        # (lists as long as these are cut by number, so that its 0 has the bits of this size)
         u = B.unit_pairs(int(state["idx"].shape[0]))
         wl0 = dataclasses.replace(wl, geom=dataclasses.replace(wl.geom, mirror=0, tile_waves=waves, unit_pairs=u))
         ms0, prof0, n0, st0 = forward_leg(wl0, max(1, min(args.steps, 3)), 1)
@@ -305,11 +306,10 @@ def bench_tilted(args):
 # Gaussian: 3 subtractions, max3, compare, sum of squares (3), scale (1), accumulate (1)
 # and one exp2; Hosemann: 3 subtractions, max3, compare, 3 denominators, 2 products,
 # accumulate and three cosines and one reciprocal.
-# issue slots per useful evaluation of the adjoint kernel (k_profile_adj, Laue), the |y| + tiny
-# guards not credited as in the forward: 39 full-rate operations (support test 5, the product
-# of the y 2, the three sinc factors 8, their squares and product 5, G P and the three weighted
-# sums 4, the three d/dN_i terms 15) and 3 sin + 3 cos + 1 rcp
-ADJ_SLOTS_PER_EVAL = 39 + 7 * TRANS_SLOTS
+# issue slots per useful evaluation of the adjoint kernel (k_profile_adj_units, Laue): 24 full-rate
+# operations (support test 5, the three sinc factors 3, their product and its square 4 with omega's,
+# the three weighted sums 3, the three d/dN_i terms 9) and 3 sin + 3 cos + 3 rcp
+ADJ_SLOTS_PER_EVAL = 24 + 9 * TRANS_SLOTS
 SLOTS_PER_EVAL_LS = {"gaussian": 10 + 1 * TRANS_SLOTS, "hosemann": 11 + 4 * TRANS_SLOTS}
 
 
@@ -496,7 +496,8 @@ def main():
     }
     if wl.geom.mirror and not args.no_unfolded and not args.only_headline:
         # the same forward step without the folds, for reference (with the folded launch's pairs
-        # per work unit, so that the computed pixels can be compared bit for bit)
+        # per work unit, so that the computed pixels can be compared bit for bit: lists as long as
+        # these are cut by number, so that its 0 has the bits of this size)
         u = B.unit_pairs(int(state["idx"].shape[0]))
         wl0 = dataclasses.replace(wl, geom=dataclasses.replace(wl.geom, mirror=0, tile_waves=waves_main, unit_pairs=u))
         ms0, prof0, n0, st0 = forward_leg(wl0, 1, 1)
