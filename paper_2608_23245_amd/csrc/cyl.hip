@@ -22,6 +22,7 @@
 #include "internal.h"
 #include "profile_common.h"
 #include "profile_tile.h"
+#include "ranges.h"
 
 namespace fdtbx {
 

@@ -12,6 +12,7 @@
 
 #include "frame.h"
 #include "internal.h"
+#include "ranges.h"
 
 namespace fdtbx {
 
@@ -379,7 +380,7 @@ __device__ static void profile_record(const PrepParams& p, const double* hh, con
       const double w = p.lineshape == FDTBX_LINESHAPE_HOSEMANN ? 0.5 : p.m / N[i];
       e = e + w * fabs(dotv(&p.f.s[3 * i], vs[v]));
     }
-    o[RS_RHO + v] = (float)e;
+    o[RS_RHO + v] = (float)(v > 0 ? widened_extent(e, r0) : e);
   }
   for (int i = 0; i < 3; ++i) {
     // ring direction at the reflection's azimuth, for query points off that azimuth

@@ -191,7 +191,7 @@ enum ReflSlot {
   RS_CS = 22,      // (e_perp.S, S_z)
   RS_C1 = 24,      // (e_perp.e1, e1_z)
   RS_C2 = 26,      // (e_perp.e2, e2_z)
-  RS_RHO = 28,     // support extent along S, e1, e2: sum_i w_i |a*_i.v|  (28..30)
+  RS_RHO = 28,     // support extent along S, e1, e2: sum_i w_i |a*_i.v|  (28..30), along e1, e2 widened_extent
   RS_AZ = 31,      // e_az.S, e_az.e1, e_az.e2 with e_az = z x e_perp (31..33)
   RS_TA = 34,      // scale_i (a_i.e_az), the lattice offset along the ring direction (34..36)
   RS_F2 = 37,      // |F|^2

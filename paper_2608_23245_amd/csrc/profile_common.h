@@ -7,7 +7,6 @@
 #include <math.h>
 
 #include "internal.h"
-#include "ranges.h"
 
 namespace fdtbx {
 
@@ -166,15 +165,15 @@ __device__ __forceinline__ void load_pair(const float* __restrict__ rec, PairRec
 // Node index range that query points p with p.S in [sl, sh], p.e1 in [l1, h1] and
 // p.e2 in [l2, h2] can reach.  A node in the support of p satisfies |s.v - p.v| <= rho_v
 // for v in {S, e1, e2} (rho_v: support extents); s.S = r0 c is in [r0 cmin, r0];
-// d_j = (s.e_j)/(s.S).  rho_1 and rho_2 are widened by the rounding of p.e1 and p.e2 (widened_reach);
-// an eighth of a node of margin on each side absorbs that of the reciprocals and of the place on the
-// grid, a few parts in 10^7 of |d_j| <= 2 T, which is n times that in nodes (1e-4 at n = 256).  A
-// whole node, as it was, made the window of a coarse grid, a few nodes wide, about half as large
-// again, and its scan is what a pair with few nodes costs: 0.377 -> 0.350 ms for 20 Hosemann nodes per side at 6 entries a pair,
-// 0.565 -> 0.545 ms for a draft of 24 Laue nodes.
+// d_j = (s.e_j)/(s.S).  The record's rho_1 and rho_2 cover the rounding of p.e1 and p.e2
+// (widened_extent); an eighth of a node of margin on each side absorbs that of the reciprocals and of
+// the place on the grid, a few parts in 10^7 of |d_j| <= 2 T, which is n times that in nodes (1e-4 at
+// n = 256).  A whole node, as it was, made the window of a coarse grid, a few nodes wide, about half
+// as large again, and its scan is what a pair with few nodes costs: 0.377 -> 0.350 ms for 20 Hosemann
+// nodes per side at 6 entries a pair, 0.565 -> 0.545 ms for a draft of 24 Laue nodes.
 __device__ static inline bool node_window_ranges(const ProfParams& q, float r0, float sl, float sh, float l1, float h1,
                                                  float l2, float h2, float rhoS, float rho1, float rho2, Window* w) {
-  const float rS = rhoS * 1.0001f, r1 = widened_reach(rho1, r0), r2 = widened_reach(rho2, r0);
+  const float rS = rhoS * 1.0001f, r1 = rho1 * 1.0001f, r2 = rho2 * 1.0001f;
   float dlo_s = fmaxf(sl - rS, r0 * q.cmin * 0.9999f);
   float dhi_s = fminf(sh + rS, r0 * 1.0001f);
   if (!(dlo_s <= dhi_s)) return false;

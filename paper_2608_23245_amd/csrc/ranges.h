@@ -16,10 +16,10 @@ namespace fdtbx {
 constexpr int kNoRingFirst = 1 << 30, kNoRingLast = -(1 << 30);
 FDTBX_HD inline bool ring_block_meets(int jl, int jh, int jb, int n) { return jb <= jh && jb + n > jl; }
 
-// Half-width of a support along e1 or e2 (its extent rho about a node at radius r0), widened by the
-// float32 rounding of the query point's coordinate there: the sum of two products of rounded factors
-// is off by up to 5 2^-24 of |p| ~ r0 however small it is, 3e-7 r0, which is several nodes of a grid
-// whose half extent is 1e-4 or less.
-FDTBX_HD inline float widened_reach(float rho, float r0) { return rho * 1.0001f + 1.0e-6f * r0; }
+// Extent of a support along e1 or e2, rho at a reflection of radius r0, as the node windows take it:
+// widened by the float32 rounding of the query point's coordinate there, the sum of two products of
+// rounded factors, which is off by up to 5 2^-24 of |p| ~ r0 however small it is, 3e-7 r0.  That is
+// several nodes of a grid whose half extent is 1e-4 or less.
+FDTBX_HD inline double widened_extent(double rho, double r0) { return rho + 1.0e-6 * r0; }
 
 }  // namespace fdtbx

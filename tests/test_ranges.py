@@ -13,7 +13,7 @@ SOURCE = """
 #include "ranges.h"
 extern "C" int ring_block_meets(int jl, int jh, int jb, int n) { return fdtbx::ring_block_meets(jl, jh, jb, n); }
 extern "C" int no_ring(int last) { return last ? fdtbx::kNoRingLast : fdtbx::kNoRingFirst; }
-extern "C" float widened_reach(float rho, float r0) { return fdtbx::widened_reach(rho, r0); }
+extern "C" double widened_extent(double rho, double r0) { return fdtbx::widened_extent(rho, r0); }
 """
 
 
@@ -26,7 +26,7 @@ def ranges(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-ffp-contract=off", "-I", CSRC, str(src), "-o", lib],
                    check=True)
     lib = ctypes.CDLL(lib)
-    lib.widened_reach.restype, lib.widened_reach.argtypes = ctypes.c_float, [ctypes.c_float, ctypes.c_float]
+    lib.widened_extent.restype, lib.widened_extent.argtypes = ctypes.c_double, [ctypes.c_double, ctypes.c_double]
     return lib
 
 
@@ -52,15 +52,14 @@ def f32(x):
     return np.asarray(x, dtype=np.float64).astype(F32)
 
 
-def window(n, T, axes, R, Z, r0, rho, widened):
+def window(n, T, axes, R, Z, r0, rho):
     """The node window of a pixel (R, Z), in the float32 operations of pair_setup and
-    node_window_ranges: axes are the (R, Z) coefficients of S, e1, e2."""
+    node_window_ranges: axes are the (R, Z) coefficients of S, e1, e2, rho the record's extents."""
     inv_h, T32, r0 = f32(n / (2 * T)), f32(T), f32(r0)
     cmin = f32(1 / np.sqrt(1 + 2 * T * T))
     R, Z = f32(R), f32(Z)
     pS, p1, p2 = [(f32(c[0]) * R).astype(F32) + (f32(c[1]) * Z).astype(F32) for c in axes]
-    rS = f32(rho[0]) * F32(1.0001)
-    r1, r2 = [np.array([widened(float(a), float(b)) for a, b in zip(f32(r), r0)], dtype=F32) for r in rho[1:]]
+    rS, r1, r2 = [f32(r) * F32(1.0001) for r in rho]
     lo, hi = np.maximum(pS - rS, r0 * cmin * F32(0.9999)), np.minimum(pS + rS, r0 * F32(1.0001))
     inv_lo, inv_hi = (F32(1) / lo).astype(F32), (F32(1) / hi).astype(F32)
     big, out = F32(2) * T32, []
@@ -95,7 +94,7 @@ def test_window_holds_every_node_in_reach(ranges, lo, hi):
     p = node * [1, 0, 1] + (T * r0 * 10 ** rng.uniform(-4, 0, N) * rng.choice([-1, 1], N))[:, None] * u
     # the reach along each axis: as far as the pixel lies from the node
     rho = [np.abs(((p - node) * e).sum(1)) * (1 + 1e-9) for e in (S, e1, e2)]
-    ok, (l1, h1, l2, h2) = window(n, T, [(e[:, 0], e[:, 2]) for e in (S, e1, e2)], p[:, 0], p[:, 2], r0, rho,
-                                  ranges.widened_reach)
+    rho[1:] = [np.array([ranges.widened_extent(*v) for v in zip(r, r0)]) for r in rho[1:]]
+    ok, (l1, h1, l2, h2) = window(n, T, [(e[:, 0], e[:, 2]) for e in (S, e1, e2)], p[:, 0], p[:, 2], r0, rho)
     missed = ~ok | (i1 < l1) | (i1 > h1) | (i2 < l2) | (i2 > h2)
     assert not missed.any(), f"{missed.sum()} of {N}"
