@@ -498,8 +498,7 @@ static void recip_basis(const fdtbx_cell* cell, double* as) {
 // (a set-up that fills 4 of 64 lanes).  Four waves in a workgroup ran 3 to 9% slower than one.
 constexpr int64_t kAdjFewItems = 8192;
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_b_profile_adj(const fdtbx_batch_entry* __restrict__ ent, const int64_t* __restrict__ items,
-                                                      int64_t n_items, int lg_parts, int chunk,
-                                                      const float* __restrict__ refl,
+                                                      int parts, int chunk, const float* __restrict__ refl,
                                                       const float* __restrict__ nodes, const double* __restrict__ pix,
                                                       const double* __restrict__ tile, const int64_t* __restrict__ rowptr,
                                                       const int32_t* __restrict__ idx, const float* __restrict__ grad_image,
@@ -509,10 +508,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_
   __shared__ __align__(16) float gw[128];
   __shared__ int bq[64];
   __shared__ int qk[128];  // node indices of the queue (the Hosemann support edge)
-  const int64_t b = launch_index();
-  if (b >> lg_parts >= n_items) return;  // uniform
-  const int parts = 1 << lg_parts, part = (int)b & (parts - 1);
-  const int64_t packed = items[b >> lg_parts];
+  const int part = (int)(blockIdx.x % (unsigned)parts);
+  const int64_t packed = items[blockIdx.x / (unsigned)parts];
   const int m = (int)(packed >> 40);
   const int t = (int)(packed & ((1ll << 40) - 1));
   const fdtbx_batch_entry& e = ent[m];
@@ -723,10 +720,11 @@ int launch_batch_backward(const fdtbx_batch_entry* ent, int32_t n_models, const 
     hipLaunchKernelGGL(k_zero_f64, dim3((unsigned)ceil_div(6 * n_hkl_total, 256)), dim3(256), 0, s, sums, 6 * n_hkl_total);
     FDTBX_LAUNCH_CHECK("batch adjoint zero");
   }
-  if (n_items > 0) {
-    const int lg_parts = n_items < kAdjFewItems ? 6 : 4, chunk = n_items < kAdjFewItems ? 4 : 16;
-    hipLaunchKernelGGL(k_b_profile_adj, launch_grid(n_items << lg_parts), dim3(64), 0, s, ent, items, n_items, lg_parts, chunk,
-                       refl, nodes, pix, tile, rowptr, idx, grad_image, sums, fixed ? fixed->partials : nullptr);
+  const int parts = n_items < kAdjFewItems ? 64 : 16, chunk = n_items < kAdjFewItems ? 4 : 16;
+  for (int64_t first = 0; first < n_items; first += kGridRow / parts) {
+    const int64_t n = min64(n_items - first, kGridRow / parts);
+    hipLaunchKernelGGL(k_b_profile_adj, dim3((unsigned)(n * parts)), dim3(64), 0, s, ent, items + first, parts, chunk, refl,
+                       nodes, pix, tile, rowptr, idx, grad_image, sums, fixed ? fixed->partials : nullptr);
     FDTBX_LAUNCH_CHECK("batch profile adjoint");
   }
   if (fixed && n_hkl_total > 0) {

@@ -45,17 +45,15 @@ inline int32_t lcols_of(const fdtbx_geometry* g) { return (g->mirror & 1) ? (til
 inline int32_t lrows_of(const fdtbx_geometry* g) { return (g->mirror & 2) ? (tiles_y_of(g) + 1) / 2 : tiles_y_of(g); }
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// The grid of a launch of n > 0 workgroups, whose indices (launch_index) pass n - 1 in its last row.
-// HIP counts the threads along x in 32 bits: 2^32 of them are refused, of more only the excess runs,
-// without an error.  2^21 workgroups of up to 1024 threads stay below.
-constexpr int kLgGridRow = 21;
+// Workgroups along x of one launch: HIP counts the threads along a dimension in 32 bits, 2^32 of them are
+// refused, of more only the excess runs, without an error.  2^21 workgroups of up to 1024 threads stay
+// below.  More go into rows along y (launch_grid; launch_index passes n - 1 in the last row), or, for
+// the batched kernels, into launches of their own, which leave the kernels as they are.
+constexpr int64_t kGridRow = int64_t{1} << 21;
 inline dim3 launch_grid(int64_t n) {
-  const int64_t row = int64_t{1} << kLgGridRow;
-  return n <= row ? dim3((unsigned)n) : dim3((unsigned)row, (unsigned)ceil_div(n, row));
+  return n <= kGridRow ? dim3((unsigned)n) : dim3((unsigned)kGridRow, (unsigned)ceil_div(n, kGridRow));
 }
-// (the row's length as a constant: gridDim would be a load at the start of every wave, 1 % of a launch
-// of 50,000 short ones)
-__device__ inline int64_t launch_index() { return ((int64_t)blockIdx.y << kLgGridRow) + blockIdx.x; }
+__device__ inline int64_t launch_index() { return kGridRow * blockIdx.y + blockIdx.x; }
 
 // Groups of threads that share the terms of a thread's sum in the batched structure factors and
 // their adjoint, for n blocks of 256 sums each: a batch of a few small models has tens of blocks,

@@ -446,18 +446,21 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_
 // (u - unit_ptr[k])-th of item k = unit_item[u] and writes its 128 pixel sums to a slot of its
 // own; k_b_unit_reduce adds an item's units in their order.  A list longer than the others (a
 // large model's tiles beside the beam hold 50 times the mean) then runs on many waves: with one
-// wave per item the longest list took 120 ms, nearly half of a forward of 32 models.
+// wave per item the longest list took 120 ms, nearly half of a forward of 32 models.  MANY: this launch's
+// units start at unit `first` (of a launch that kMaxUnits would not hold); without that scalar the kernel
+// keeps its registers for the walk (nine models of up to 192 x 192 pixels 1.13 ms with it, 1.07 without).
+constexpr int64_t kMaxUnits = (int64_t{1} << 26) - 1;  // 64 threads each, 2^32 along one dimension
+template <bool MANY>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_b_profile_units(
     const fdtbx_batch_entry* __restrict__ ent, const int64_t* __restrict__ soff, const int64_t* __restrict__ items,
-    const int64_t* __restrict__ unit_ptr, const int32_t* __restrict__ unit_item, int64_t n_units, int64_t U,
+    const int64_t* __restrict__ unit_ptr, const int32_t* __restrict__ unit_item, int64_t first, int64_t U,
     const float* __restrict__ refl, const float* __restrict__ nodes, const double* __restrict__ pix,
     const double* __restrict__ tile, const double* __restrict__ stile, const int64_t* __restrict__ srowptr,
     const int32_t* __restrict__ sidx, float* __restrict__ image, float* __restrict__ partials) {
   __shared__ float4 qn[128];
   __shared__ int bq[64];
   __shared__ int qk[128];  // node indices of the queue (the Hosemann support edge)
-  const int64_t u = launch_index();
-  if (u >= n_units) return;
+  const int64_t u = MANY ? first + blockIdx.x : blockIdx.x;
   const int k = unit_item[u];
   StackedItem it;
   stacked_item(ent, soff, items[k], refl, nodes, pix, tile, stile, srowptr, sidx, image, it);
@@ -471,11 +474,10 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_
 
 __global__ void __launch_bounds__(64) k_b_unit_reduce(
     const fdtbx_batch_entry* __restrict__ ent, const int64_t* __restrict__ soff, const int64_t* __restrict__ items,
-    int64_t n_items, const int64_t* __restrict__ unit_ptr, const double* __restrict__ pix, const double* __restrict__ tile,
+    const int64_t* __restrict__ unit_ptr, const double* __restrict__ pix, const double* __restrict__ tile,
     const double* __restrict__ stile, const int64_t* __restrict__ srowptr, float* __restrict__ image,
     const float* __restrict__ partials) {
-  const int64_t k = launch_index();
-  if (k >= n_items) return;
+  const int64_t k = blockIdx.x;
   StackedItem it;
   stacked_item(ent, soff, items[k], nullptr, nullptr, pix, tile, stile, srowptr, nullptr, image, it);
   float sa = 0.0f, sb = 0.0f;
@@ -494,14 +496,15 @@ int launch_batch_profile_units(const fdtbx_batch_entry* ent, const int64_t* soff
                                int64_t unit_pairs, const float* refl, const float* nodes, const double* pix,
                                const double* tile, const double* stile, const int64_t* srowptr, const int32_t* sidx,
                                float* image, float* partials, hipStream_t s) {
-  if (n_units > 0) {
-    hipLaunchKernelGGL(k_b_profile_units, launch_grid(n_units), dim3(64), 0, s, ent, soff, items, unit_ptr, unit_item,
-                       n_units, unit_pairs, refl, nodes, pix, tile, stile, srowptr, sidx, image, partials);
+  for (int64_t first = 0; first < n_units; first += kMaxUnits) {
+    hipLaunchKernelGGL(n_units > kMaxUnits ? k_b_profile_units<true> : k_b_profile_units<false>,
+                       dim3((unsigned)min64(n_units - first, kMaxUnits)), dim3(64), 0, s, ent, soff, items, unit_ptr,
+                       unit_item, first, unit_pairs, refl, nodes, pix, tile, stile, srowptr, sidx, image, partials);
     FDTBX_LAUNCH_CHECK("batch profile units");
   }
-  if (n_items > 0) {
-    hipLaunchKernelGGL(k_b_unit_reduce, launch_grid(n_items), dim3(64), 0, s, ent, soff, items, n_items, unit_ptr, pix, tile,
-                       stile, srowptr, image, (const float*)partials);
+  for (int64_t first = 0; first < n_items; first += kGridRow) {
+    hipLaunchKernelGGL(k_b_unit_reduce, dim3((unsigned)min64(n_items - first, kGridRow)), dim3(64), 0, s, ent, soff,
+                       items + first, unit_ptr + first, pix, tile, stile, srowptr, image, (const float*)partials);
     FDTBX_LAUNCH_CHECK("batch profile unit sums");
   }
   return FDTBX_OK;

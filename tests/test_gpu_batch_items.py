@@ -59,3 +59,26 @@ def test_forward_unit_sums(n):
     got = be.forward()
     torch.cuda.synchronize()
     assert torch.equal(got, want)
+
+
+def test_forward_units_beyond_one_launch():
+    """2^26 units of empty lists, 1024 to each of 65536 items of a tile that nothing reaches, before the
+    batch's own: those are then in the second of two launches (34 GB of unit sums)."""
+    be = engine()
+    want = be.forward().clone()
+    empty = be.stack_items[-1:]
+    assert be.unit_ptr[-1] == be.unit_ptr[-2] == be.n_units
+    ahead = torch.arange(0, 1 << 26, 1024, device="cuda")
+    be.stack_items = torch.cat([empty.expand(1 << 16), be.stack_items]).contiguous()
+    be.unit_ptr = torch.cat([ahead, be.unit_ptr + (1 << 26)]).contiguous()
+    be.unit_item = torch.cat([torch.arange(1 << 16, dtype=torch.int32, device="cuda").repeat_interleave(1024),
+                              be.unit_item + (1 << 16)]).contiguous()
+    be.n_units += 1 << 26
+    be.unit_sums = torch.empty((be.n_units, 128), dtype=torch.float32, device="cuda")
+    be.image.fill_(-1.0)
+    print(f"{be.n_units} units", flush=True)
+    got = be.forward()
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    be.unit_sums = None
+    torch.cuda.empty_cache()
