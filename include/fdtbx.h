@@ -745,7 +745,7 @@ int fdtbx_batch_forward(const fdtbx_batch_entry* entries, int32_t n_models, cons
  *   counter    device int64 [2] scratch (the work queue)
  * The sums run in another grouping than the per-tile launch's, so the images agree with it to
  * float32 rounding.  For callers without unit tables: fdtbx_batch_profile_units, which cuts the
- * lists, is the faster one wherever their lengths differ (32 ragged models 281 / 122 ms).  Does not
+ * lists, is the faster one wherever their lengths differ (32 ragged models 252 / 116 ms).  Does not
  * allocate, copy to the host or synchronise. */
 int fdtbx_batch_profile_stacked(const fdtbx_batch_entry* entries, int32_t n_models, const int64_t* stack_off,
                                 const int64_t* stack_items, int64_t n_items, const float* refl, const float* nodes,
