@@ -143,16 +143,6 @@ int launch_adjoint_units(const fdtbx_model* model, const float* refl, const floa
                                                 partials, T, s);
 }
 
-__global__ void k_zero_f64(double* __restrict__ v, int64_t n) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n) v[k] = 0.0;
-}
-
-__global__ void k_zero_f32(float* __restrict__ v, int64_t n) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n) v[k] = 0.0f;
-}
-
 // ---------------------------------------------------------------- fixed-order reduction
 // The sums of lanes 0..L-1 of each group of L lanes (a power of two) by a fixed tree; lane 0 of
 // the group holds them.
@@ -717,8 +707,8 @@ int launch_batch_backward(const fdtbx_batch_entry* ent, int32_t n_models, const 
     const int rc = fill(fixed->partials, 12 * fixed->n_pairs, 0.0f, s);
     if (rc) return rc;
   } else {
-    hipLaunchKernelGGL(k_zero_f64, dim3((unsigned)ceil_div(6 * n_hkl_total, 256)), dim3(256), 0, s, sums, 6 * n_hkl_total);
-    FDTBX_LAUNCH_CHECK("batch adjoint zero");
+    const int rc = fill(sums, 6 * n_hkl_total, 0.0, s);
+    if (rc) return rc;
   }
   const int parts = n_items < kAdjFewItems ? 64 : 16, chunk = n_items < kAdjFewItems ? 4 : 16;
   for (int64_t first = 0; first < n_items; first += kGridRow / parts) {
@@ -789,8 +779,8 @@ extern "C" int fdtbx_profile_adjoint(const fdtbx_model* model, const float* refl
   if (!refl || !nodes || !pix || !tile || !offsets || !idx || !grad_image || !sums)
     return fail(FDTBX_ERR_INVALID_ARGUMENT, "null pointer");
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_zero_f64, dim3((unsigned)ceil_div(6 * n_hkl, 256)), dim3(256), 0, s, sums, 6 * n_hkl);
-  FDTBX_LAUNCH_CHECK("adjoint zero");
+  rc = fill(sums, 6 * n_hkl, 0.0, s);
+  if (rc) return rc;
   return launch_profile_adjoint(model, refl, nodes, pix, tile, offsets, idx, order, n_hkl, grad_image, sums, nullptr, s);
 }
 
@@ -812,8 +802,8 @@ extern "C" int fdtbx_profile_adjoint_balanced(const fdtbx_model* model, const fl
   const UnitLayout L = unit_layout(q, order != nullptr, pair_cap, model->geom.unit_pairs);
   if (bal_ws_bytes < L.total) return fail(FDTBX_ERR_BUFFER_TOO_SMALL, "balanced workspace too small");
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_zero_f64, dim3((unsigned)ceil_div(6 * n_hkl, 256)), dim3(256), 0, s, sums, 6 * n_hkl);
-  FDTBX_LAUNCH_CHECK("adjoint zero");
+  rc = fill(sums, 6 * n_hkl, 0.0, s);
+  if (rc) return rc;
   // the forward launch is done with its queue counters: the adjoint takes them over
   return launch_adjoint_units(model, refl, nodes, pix, tile, offsets, idx, order, pair_cap, bal_ws,
                               (int32_t*)((char*)bal_ws + L.ctr), n_hkl, grad_image, sums, nullptr, s);
@@ -830,8 +820,8 @@ extern "C" int fdtbx_profile_adjoint_pairs(const fdtbx_model* model, const float
   if (pair_cap == 0) return FDTBX_OK;
   if (!partials) return fail(FDTBX_ERR_INVALID_ARGUMENT, "null pointer");
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_zero_f32, dim3((unsigned)ceil_div(12 * pair_cap, 256)), dim3(256), 0, s, partials, 12 * pair_cap);
-  FDTBX_LAUNCH_CHECK("adjoint partials zero");
+  rc = fill(partials, 12 * pair_cap, 0.0f, s);
+  if (rc) return rc;
   if (n_hkl == 0) return FDTBX_OK;
   if (!refl || !nodes || !pix || !tile || !offsets || !idx || !grad_image)
     return fail(FDTBX_ERR_INVALID_ARGUMENT, "null pointer");

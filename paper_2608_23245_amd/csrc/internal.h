@@ -63,13 +63,13 @@ inline int batch_split(int64_t n) { return n <= 64 ? 16 : (n <= 256 ? 4 : 1); }
 // v[0..n) = x, by a kernel (hipMemsetAsync nodes do not belong in captured graphs).
 template <class T>
 __global__ void k_fill(T* __restrict__ v, int64_t n, T x) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t i = launch_index() * 256 + threadIdx.x;
   if (i < n) v[i] = x;
 }
 template <class T>
 inline int fill(T* v, int64_t n, T x, hipStream_t s) {
   if (n <= 0 || !v) return FDTBX_OK;
-  hipLaunchKernelGGL(k_fill<T>, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, v, n, x);
+  hipLaunchKernelGGL(k_fill<T>, launch_grid(ceil_div(n, 256)), dim3(256), 0, s, v, n, x);
   FDTBX_LAUNCH_CHECK("fill");
   return FDTBX_OK;
 }

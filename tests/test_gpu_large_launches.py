@@ -87,3 +87,23 @@ def test_pair_reduction_of_many_reflections(n):
         at += m
     sums[rows] = 0.0
     assert torch.count_nonzero(sums).item() == 0
+
+
+def test_clearing_of_many_partials():
+    """Per-pair sums of 2^32 values and more (358 million pairs of capacity): cleared to the last."""
+    wl = W.small(93)
+    model = B.make_model(wl)
+    hkl = B.enumerate_hkl(model.cell, wl.quad.d_min, wl.quad.d_max)
+    _, F2 = B.structure_factors(model.cell, atoms_to_device(wl.atoms), hkl, want_F=False)
+    refl, cull = B.reflection_prep(model, hkl, F2)
+    pix, tile = B.pixel_map(model.geom)
+    off, idx = B.cull(model.geom, tile, cull)
+    cap = (1 << 32) // 12 + 1
+    part = torch.full((cap, 12), -1.0, device="cuda")
+    G = torch.zeros((wl.geom.height, wl.geom.width), device="cuda")
+    p = B._ptr
+    print(f"{cap} pairs of capacity, {idx.numel()} listed", flush=True)
+    B._check(B.lib().fdtbx_profile_adjoint_pairs(ctypes.byref(model), p(refl), p(B.node_table(model)), p(pix), p(tile), p(off), p(idx),
+                                                 None, int(hkl.shape[0]), cap, p(G), p(part), B._stream()))
+    torch.cuda.synchronize()
+    assert torch.count_nonzero(part).item() == 0
